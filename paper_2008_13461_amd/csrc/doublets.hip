@@ -67,16 +67,6 @@ __device__ __forceinline__ bool doublet_pass(const DevCfg& k, double tdphi, doub
 
 namespace {
 
-// Four values of the input type in one vector (one load).
-template <class T>
-struct Vec4Of;
-template <>
-struct Vec4Of<float> { using type = float4; };
-template <>
-struct Vec4Of<double> { using type = double4; };
-template <class T>
-using Vec4 = typename Vec4Of<T>::type;
-
 template <class T>
 struct HitsIn {
   int32_t n_hits, n_events;

@@ -6,14 +6,14 @@
 //   1. the stored cells are indexed by outer hit with the index of the link
 //      step (blocks of consecutive cells grouped by outer hit in LDS, one
 //      segment per block and hit; no per-cell atomic);
-//   2. one wavefront per outer hit gathers the hit's cells into LDS (cell,
-//      inner hit's coordinates), counting-sorted by a polar-direction key of
-//      the vector to the outer hit into buckets at least as wide as the cut
-//      angle, and tests each cell (one lane each) only against the cells of
-//      its own and the neighbouring buckets (and of those around its negated
-//      key: nearly opposite vectors); the exact test, in double, decides and
-//      clears the cell's keep flag.  Hits with more cells than a wavefront
-//      stages are listed and done by one work-group each;
+//   2. a team of threads per outer hit gathers the hit's cells into LDS,
+//      counting-sorted by a polar-direction key of the vector to the outer hit
+//      into buckets at least as wide as the cut angle, and tests each cell
+//      only against the cells of its own and the neighbouring buckets (and of
+//      those around its negated key: nearly opposite vectors); a dot product
+//      in single precision filters the pairs, the exact test, in double,
+//      decides and clears the cell's keep flag.  Hits with more cells than a
+//      team stages are listed for the next larger one;
 //   3. the kept cells are compacted in their order (a scan of the flags),
 //      through a copy in the workspace, and each inner hit's range of cells
 //      is moved with them.
@@ -22,7 +22,6 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
-#include <type_traits>
 
 #include "pt_internal.h"
 
@@ -32,9 +31,9 @@ namespace pt {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kWaves = kBlock / kWave;
-constexpr int kCapSmall = 256;  // cells per outer hit staged in LDS by the first kernel
-constexpr int kCap = 512;       // by the second (the hits with more than kCapSmall)
+constexpr int kTiers = 3;  // kernels that stage an outer hit's cells in LDS, by their number:
+constexpr int kTierCap[kTiers] = {256, 512, 1024};           // at most so many ...
+constexpr int kTierTeam[kTiers] = {kWave, 2 * kWave, kBlock};  // ... with so many threads
 constexpr int kNB = 256;       // most key buckets
 constexpr int32_t kHitMask = 0x7fffffff;
 
@@ -47,7 +46,7 @@ struct FbArgs {
   double theta2;
   int32_t nb;             // key buckets: each at least the cut angle wide
   float kwin;             // key window: asin(theta) with a margin, 2 when theta >= 1
-  float phwin;            // azimuth window of vectors at least kS0 transverse, > pi: none
+  float cos2_min;         // squared cosine, in single precision, below which two vectors are not aligned
   const int32_t* count;   // cells found
   int32_t cap;
   int32_t* inner;
@@ -58,10 +57,8 @@ struct FbArgs {
   OuterIndex idx;
   // workspace
   int32_t* keep;          // [cap + 1] flags, then positions
-  int32_t* mid;           // [n_hits] outer hits with more than kCapSmall cells
-  int32_t* n_mid;
-  int32_t* big;           // [n_hits] outer hits with more than kCap cells
-  int32_t* n_big;
+  int32_t* list[kTiers];  // [n_hits] outer hits with more cells than tier i stages
+  int32_t* n_list;        // [kTiers] how many
   int32_t* t_inner;       // [cap] compacted copies
   int32_t* t_outer;
   uint8_t* t_pair;
@@ -86,41 +83,6 @@ __device__ inline float polar_key(double ux, double uy, double uz) {
   return l > 0.f ? float(uz) / l : 0.f;
 }
 
-// Azimuth of a vector whose transverse part is at least kS0 of its length,
-// else kNoPhi.  Two such vectors at an angle a <= kS0 have transverse parts
-// at most a apart, hence azimuths at most asin(a / kS0) apart (for nearly
-// opposite vectors, pi minus that).
-constexpr float kS0 = 0.2f;
-constexpr float kNoPhi = 10.f;
-__device__ inline float azimuth(double ux, double uy, double uz) {
-  const float t2 = float(ux * ux + uy * uy), l2 = t2 + float(uz * uz);
-  return t2 >= (kS0 * kS0) * l2 ? atan2f(float(uy), float(ux)) : kNoPhi;
-}
-
-// Azimuths are staged as 16-bit quanta of 2 pi / 65535 (kNoPhiQ: none).
-// The test on quanta accepts every pair whose float azimuths are within the
-// window (a quantum is the floor of the scaled azimuth, so two are at most
-// one quantum further apart than the azimuths, and the window is widened by
-// two quanta): it stays a filter in front of the exact test.
-constexpr float kPhiScale = 65535.f / 6.28318531f;
-constexpr int kNoPhiQ = 0xFFFF;
-__device__ inline uint16_t phi_quantum(float phi) {
-  if (phi == kNoPhi) return kNoPhiQ;
-  const int q = static_cast<int>((phi + 3.14159265f) * kPhiScale);
-  return static_cast<uint16_t>(min(max(q, 0), kNoPhiQ - 1));
-}
-// The window in quanta (the whole circle when the azimuth test is off).
-__device__ inline int phi_window_q(float win) {
-  return win >= 3.2f ? 65535 : static_cast<int>(ceilf(win * kPhiScale)) + 2;
-}
-// Whether two azimuths allow an angle within the cut (opp: nearly opposite).
-__device__ inline bool phi_ok(int qi, int qj, int wq, bool opp) {
-  if (qi == kNoPhiQ || qj == kNoPhiQ) return true;
-  int d = abs(qi - qj);
-  d = min(d, 65535 - d);
-  return opp ? 2 * d >= 65535 - 2 * wq : d <= wq;
-}
-
 // Bucket of a key in [-1, 1] among nb buckets of width 2 / nb.
 __device__ inline int bucket(float k, int nb) {
   const int b = static_cast<int>((k + 1.f) * (0.5f * static_cast<float>(nb)));
@@ -138,7 +100,7 @@ __device__ inline bool kills(double ux, double uy, double uz, double U2, double 
 }
 
 template <class T>
-__device__ inline void vec(const FbArgs<T>& a, double Xh, double Yh, double Zh, int i, double& ux, double& uy,
+__device__ inline void vec_to(const FbArgs<T>& a, double Xh, double Yh, double Zh, int i, double& ux, double& uy,
                            double& uz, double& U2) {
   ux = Xh - double(a.x[i]);
   uy = Yh - double(a.y[i]);
@@ -152,147 +114,262 @@ __global__ void k_fb_flags(FbArgs<T> a) {
   for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) a.keep[c] = 1;
 }
 
-// One wavefront per outer hit.
-// CAP cells per wavefront, WAVES wavefronts per block.  Every outer hit (one
-// wavefront each) when LISTED is false, else the hits listed in a.mid (a
-// persistent grid); hits with more than CAP cells are listed for the next
-// kernel (a.mid, then a.big).
-template <class T, int CAP, int WAVES, bool LISTED>
-__global__ void __launch_bounds__(WAVES * kWave) k_fb_kill(FbArgs<T> a) {
-  __shared__ int32_t s_bin[WAVES][kNB + 1];   // cells per key bucket, then first position
-  // per staged cell: bucket | rank in it << kBkShift (16 bits when both fit 8)
-  constexpr int kBkShift = CAP <= 256 ? 8 : 16;
-  static_assert(kNB <= 256 && CAP <= 0x10000, "buckets fit 8 bits, ranks the rest");
-  using Bk = std::conditional_t<CAP <= 256, uint16_t, int32_t>;
-  __shared__ Bk s_bk[WAVES][CAP];
-  __shared__ uint16_t s_val[WAVES][CAP];      // staged cells in bucket order (16 bits: five work-groups fit per CU)
-  __shared__ int32_t s_cell[WAVES][CAP];
-  __shared__ uint16_t s_phi[WAVES][CAP];      // azimuth quanta
-  __shared__ T s_x[WAVES][CAP];               // the inner hit's coordinates
-  __shared__ T s_y[WAVES][CAP];
-  __shared__ T s_z[WAVES][CAP];
-  const int w = static_cast<int>(threadIdx.x) / kWave;
-  const int lane = __lane_id();
-  if (stored(a) == 0) return;
-  const int n_items = LISTED ? *a.n_mid : a.n_hits;
-  for (int item = blockIdx.x * WAVES + w; item < n_items; item += LISTED ? gridDim.x * WAVES : n_items) {
-  const int h = LISTED ? a.mid[item] : item;
-  const int sb = a.idx.seg_first[h], se = a.idx.seg_first[h + 1];
-  // the hit's cells: segment descriptors 64 at a time, then their entries
-  // 64 at a time (each lane finds its entry's segment among the 64)
-  int m = 0;
-  for (int s0 = sb; s0 < se; s0 += kWave) {
-    const int n = s0 + lane < se ? a.idx.seg[s0 + lane].y : 0;
-    m += wave_sum(n);
-  }
-  if (m < 2) continue;
-  const double Xh = double(a.x[h]), Yh = double(a.y[h]), Zh = double(a.z[h]);
-  if (m > CAP) {  // more cells than this kernel stages: listed for the next
-    if (lane == 0) {
-      if (LISTED) a.big[atomicAdd(a.n_big, 1)] = h;
-      else a.mid[atomicAdd(a.n_mid, 1)] = h;
-    }
-    continue;
-  }
-  const float win = a.kwin;
-  const double rh = sqrt(Xh * Xh + Yh * Yh);
-  const double nx = rh > 0.0 ? Xh / rh : 0.0, ny = rh > 0.0 ? Yh / rh : 0.0;
-  const float zs = Zh < 0.0 ? -1.f : 1.f;
-  float rmin = 2.f, zmin = 2.f;  // smallest radial and z-side keys of the lane's cells
-  wave_sync();  // the previous hit's LDS is no longer read
-  for (int b = lane; b <= a.nb; b += kWave) s_bin[w][b] = 0;
-  wave_sync();
-  int at = 0;
-  for (int s0 = sb; s0 < se; s0 += kWave) {
-    const int2 g = s0 + lane < se ? a.idx.seg[s0 + lane] : make_int2(0, 0);
-    const int incl = wave_incl_scan(g.y);
-    const int excl = incl - g.y;
-    const int tot = __shfl(incl, kWave - 1);
-    for (int f0 = 0; f0 < tot; f0 += kWave) {  // wave-uniform: every lane takes part in the shuffles
-      const int f = f0 + lane;
-      // the last lane whose segment starts at or before f
-      int j = 0;
+// Barrier and reductions over the TEAM threads (a wavefront, or the whole
+// block) that work on one outer hit.
+template <int TEAM>
+__device__ __forceinline__ void team_sync() {
+  if constexpr (TEAM == kWave) wave_sync(); else __syncthreads();
+}
+
+// Inclusive prefix sum of v over the team, the total to *total; s_w holds
+// one word per wavefront of the team.
+template <int TEAM>
+__device__ inline int team_scan(int v, int32_t* s_w, int* total) {
+  const int incl = wave_incl_scan(v);
+  if constexpr (TEAM == kWave) {
+    *total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    return incl;
+  } else {
+    const int wave = static_cast<int>(threadIdx.x % TEAM) / kWave;
+    __syncthreads();  // the words of the previous scan are read
+    if (__lane_id() == kWave - 1) s_w[wave] = incl;
+    __syncthreads();
+    int before = 0, sum = 0;
 #pragma unroll
-      for (int step = kWave / 2; step > 0; step >>= 1) {
-        const int e = __shfl(excl, j + step);
-        if (e <= f) j += step;
-      }
-      const int first = __shfl(g.x, j) + (f - __shfl(excl, j));
-      if (f >= tot) continue;
-      const int2 en = a.idx.ent[first];
-      const int ih = en.y & kHitMask;
-      s_cell[w][at + f] = en.x;
-      const T hx = a.x[ih], hy = a.y[ih], hz = a.z[ih];
-      s_x[w][at + f] = hx;
-      s_y[w][at + f] = hy;
-      s_z[w][at + f] = hz;
-      const double ux = Xh - double(hx), uy = Yh - double(hy), uz = Zh - double(hz);
-      s_phi[w][at + f] = phi_quantum(azimuth(ux, uy, uz));
-      const float kz = polar_key(ux, uy, uz);
-      const int b = bucket(kz, a.nb);
-      s_bk[w][at + f] = static_cast<Bk>(b | (atomicAdd(&s_bin[w][b], 1) << kBkShift));
-      // key of the vector about the outer hit's transverse direction
-      const double ur = ux * nx + uy * ny;
-      const double ox = ux - ur * nx, oy = uy - ur * ny;
-      const float lr = sqrtf(float(ox * ox + oy * oy + uz * uz)) + fabsf(float(ur));
-      rmin = fminf(rmin, lr > 0.f ? float(ur) / lr : 0.f);
-      zmin = fminf(zmin, kz * zs);
+    for (int w = 0; w < TEAM / kWave; ++w) {
+      if (w < wave) before += s_w[w];
+      sum += s_w[w];
     }
-    at += tot;
-  }
-  // nearly opposite partners are possible only when neither family of keys
-  // stays above the cut angle for every cell of the hit (two nearly opposite
-  // vectors cannot both point away from the beam line, or both along the
-  // outer hit's side of z, by more than the cut angle)
-  const bool mirror = wave_min(rmin) <= win && wave_min(zmin) <= win;
-  wave_sync();
-  // counting sort by bucket: first positions (a scan over the buckets), then
-  // each staged cell at its bucket's first position plus its rank
-  {
-    int carry = 0;
-    for (int b0 = 0; b0 < a.nb; b0 += kWave) {
-      const int b = b0 + lane;
-      const int c = b < a.nb ? s_bin[w][b] : 0;
-      const int incl = wave_incl_scan(c);
-      if (b < a.nb) s_bin[w][b] = carry + incl - c;
-      carry += __shfl(incl, kWave - 1);
-    }
-    if (lane == 0) s_bin[w][a.nb] = carry;
-  }
-  wave_sync();
-  for (int i = lane; i < m; i += kWave) {
-    const int v = s_bk[w][i];
-    s_val[w][s_bin[w][v & ((1 << kBkShift) - 1)] + (v >> kBkShift)] = static_cast<uint16_t>(i);
-  }
-  wave_sync();
-  // each cell against the cells of its bucket and the two next to it, and of
-  // the buckets around its negated key (nearly opposite vectors); the
-  // azimuth test first, the exact test from the staged coordinates last
-  const int wq = phi_window_q(a.phwin);
-  for (int i = lane; i < m; i += kWave) {
-    const double ux = Xh - double(s_x[w][i]), uy = Yh - double(s_y[w][i]), uz = Zh - double(s_z[w][i]);
-    const double U2 = (ux * ux + uy * uy) + uz * uz;
-    bool killed = false;
-    const int nb = a.nb;
-    const float ki = polar_key(ux, uy, uz);  // the staged key, recomputed
-    const int pi = s_phi[w][i];
-    for (int pass = 0; pass < (mirror ? 2 : 1) && !killed; ++pass) {
-      const int c = bucket(pass == 0 ? ki : -ki, nb);
-      const int q0 = s_bin[w][max(c - 1, 0)], q1 = s_bin[w][min(c + 2, nb)];
-      for (int q = q0; q < q1 && !killed; ++q) {
-        const int j = s_val[w][q];
-        if (j == i || !phi_ok(pi, s_phi[w][j], wq, pass == 1)) continue;
-        const double vx = Xh - double(s_x[w][j]), vy = Yh - double(s_y[w][j]), vz = Zh - double(s_z[w][j]);
-        const double V2 = (vx * vx + vy * vy) + vz * vz;
-        killed = kills(ux, uy, uz, U2, vx, vy, vz, V2, a.theta2);
-      }
-    }
-    if (killed) a.keep[s_cell[w][i]] = 0;
-  }
+    *total = sum;
+    return before + incl;
   }
 }
 
-// The outer hits with more than kCap cells, one work-group each (a
+// Minimum of v over the team (s_w as in team_scan).
+template <int TEAM>
+__device__ inline float team_min(float v, float* s_w) {
+  v = wave_min(v);
+  if constexpr (TEAM > kWave) {
+    const int wave = static_cast<int>(threadIdx.x % TEAM) / kWave;
+    __syncthreads();
+    if (__lane_id() == 0) s_w[wave] = v;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < TEAM / kWave; ++w) v = fminf(v, s_w[w]);
+  }
+  return v;
+}
+
+// The cells of one outer hit by one team of threads, a work-group: a
+// wavefront for every hit with at most kTierCap[0] cells (tier 0; hits differ
+// in their cells by orders of magnitude, and a work-group of four wavefronts,
+// a hit each, held its slots until the slowest was done: 1.83 against 2.25
+// ms), and two or four for the hits with more, which the tier before lists (a
+// persistent grid; two against four for 257..512 cells: 1.29 against 1.48 ms).
+//
+// The cells are staged in LDS sorted by key bucket -- the unit vector to the
+// outer hit and its squared length in one 16-byte vector, the inner hit's
+// coordinates beside it -- so that a cell's candidates are contiguous and
+// neighbouring lanes, which take neighbouring cells of the sorted list, scan
+// nearly the same ones, four a step.  A candidate costs one LDS read and a
+// dot product in single precision: 1 - (n_i . n_j)^2 is the squared sine to
+// 2e-6, so that only pairs within the cut angle and not longer go on to the
+// exact test (in double, from the coordinates), which then nearly always
+// decides and is run by all lanes that found such a pair together.  With a
+// coarse azimuth filter in its place, some lane of the wavefront ran the
+// exact test in nearly every step (16 PU200 overlap events, the two kernels:
+// 9.4 ms against 3.0).  Meeting each pair once and queueing the
+// aligned ones for full wavefronts of exact tests took 3.5 ms: a cell has 3.2
+// aligned partners, and the first already decides.
+template <class T, int TIER>
+__global__ void __launch_bounds__(kTierTeam[TIER]) k_fb_kill(FbArgs<T> a) {
+  constexpr int CAP = kTierCap[TIER], TEAM = kTierTeam[TIER];
+  constexpr bool LISTED = TIER > 0;
+  constexpr int kRounds = CAP / TEAM;
+  constexpr int kStep = 4;  // candidates per step of a scan
+  static_assert(CAP % TEAM == 0, "whole rounds");
+  __shared__ float4 s_vec[CAP + kStep];  // by bucket: unit vector, squared length (NaN: in every test)
+  __shared__ T s_x[CAP];                 // by bucket: the inner hit
+  __shared__ T s_y[CAP];
+  __shared__ T s_z[CAP];
+  __shared__ int32_t s_cell[CAP];        // by bucket: the cell
+  __shared__ uint8_t s_bk[CAP];          // by bucket: the bucket
+  __shared__ int32_t s_bin[kNB + 1];     // cells per bucket, then first position
+  __shared__ int32_t s_sum[TEAM / kWave];
+  __shared__ float s_min[TEAM / kWave];
+  int32_t* s_base = reinterpret_cast<int32_t*>(s_vec);  // while the cells are gathered: per segment
+  int32_t* s_mark = s_cell;                             // ... and per cell its segment's index
+  const int t = static_cast<int>(threadIdx.x);
+  const int n_items = LISTED ? a.n_list[max(TIER - 1, 0)] : a.n_hits;
+  if (stored(a) == 0) return;
+  const int nb = a.nb;
+  for (int item = blockIdx.x; item < n_items; item += LISTED ? gridDim.x : n_items) {
+    const int h = LISTED ? a.list[max(TIER - 1, 0)][item] : item;
+    const int sb = a.idx.seg_first[h], se = a.idx.seg_first[h + 1];
+    const double Xh = double(a.x[h]), Yh = double(a.y[h]), Zh = double(a.z[h]);
+    // the hit's cells, from the sizes of its segments
+    const int2 g0 = sb + t < se ? a.idx.seg[sb + t] : make_int2(0, 0);
+    int at;
+    const int i0 = team_scan<TEAM>(g0.y, s_sum, &at);
+    int m = at;
+    for (int s0 = sb + TEAM; s0 < se; s0 += TEAM) {
+      int more;
+      team_scan<TEAM>(s0 + t < se ? a.idx.seg[s0 + t].y : 0, s_sum, &more);
+      m += more;
+    }
+    if (m < 2) continue;
+    if (m > CAP) {  // more cells than this kernel stages: listed for the next
+      if (t == 0) a.list[TIER][atomicAdd(a.n_list + TIER, 1)] = h;
+      continue;
+    }
+    team_sync<TEAM>();  // the previous hit's LDS is no longer read
+    // the index entry of each cell: a segment marks its first cell and its
+    // first in every 64, and a maximum over the 64 before finds a cell's mark
+    for (int f = t; f < m; f += TEAM) s_mark[f] = -1;
+    for (int b = t; b <= nb; b += TEAM) s_bin[b] = 0;
+    team_sync<TEAM>();
+    auto mark = [&](int s, int2 g, int first) {
+      if (g.y > 0) {
+        s_base[s] = g.x - first;
+        for (int f = first; f < first + g.y; f = (f / kWave + 1) * kWave) s_mark[f] = s;
+      }
+    };
+    mark(t, g0, i0 - g0.y);
+    for (int s0 = TEAM; s0 < se - sb; s0 += TEAM) {
+      const int2 g = sb + s0 + t < se ? a.idx.seg[sb + s0 + t] : make_int2(0, 0);
+      int more;
+      const int incl = team_scan<TEAM>(g.y, s_sum, &more);
+      mark(s0 + t, g, at + incl - g.y);
+      at += more;
+    }
+    team_sync<TEAM>();
+    int cell[kRounds], ih[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      const int f = r * TEAM + t;
+      cell[r] = -1;
+      if (r * TEAM < m) {  // uniform
+        const int s = wave_max_scan(f < m ? s_mark[f] : -1);
+        if (f < m) {
+          const int2 en = a.idx.ent[s_base[s] + f];
+          cell[r] = en.x;
+          ih[r] = en.y & kHitMask;
+        }
+      }
+    }
+    T px[kRounds], py[kRounds], pz[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      if (cell[r] >= 0) {
+        px[r] = a.x[ih[r]];
+        py[r] = a.y[ih[r]];
+        pz[r] = a.z[ih[r]];
+      }
+    }
+    // the cells' vectors, in registers until their places are known
+    const float rh = sqrtf(float(Xh) * float(Xh) + float(Yh) * float(Yh));
+    const float hx = rh > 0.f ? float(Xh) / rh : 0.f, hy = rh > 0.f ? float(Yh) / rh : 0.f;
+    const float zs = Zh < 0.0 ? -1.f : 1.f;
+    float rmin = 2.f, zmin = 2.f;  // smallest radial and z-side keys of the thread's cells
+    float4 vec[kRounds];
+    int place[kRounds];  // bucket | rank in it << 8
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      if (cell[r] < 0) continue;
+      const double dx = Xh - double(px[r]), dy = Yh - double(py[r]), dz = Zh - double(pz[r]);
+      const float ux = float(dx), uy = float(dy), uz = float(dz);
+      const float t2 = ux * ux + uy * uy;
+      // polar key: uz / (|u_T| + |uz|)
+      const float l = sqrtf(t2) + fabsf(uz);
+      const float kz = l > 0.f ? uz / l : 0.f;
+      const int b = bucket(kz, nb);
+      place[r] = b | (atomicAdd(&s_bin[b], 1) << 8);
+      // key of the vector about the outer hit's transverse direction
+      const float ur = ux * hx + uy * hy;
+      const float ox = ux - ur * hx, oy = uy - ur * hy;
+      const float lr = sqrtf(ox * ox + oy * oy + uz * uz) + fabsf(ur);
+      rmin = fminf(rmin, lr > 0.f ? ur / lr : 0.f);
+      zmin = fminf(zmin, kz * zs);
+      // the length is rounded once, so that it never orders two the wrong
+      // way; one whose square is out of range takes part in every test
+      float l2 = float((dx * dx + dy * dy) + dz * dz);
+      if (!(l2 > 1e-30f && l2 < 1e30f)) l2 = __builtin_nanf("");
+      const float inv = __builtin_amdgcn_rsqf(l2);
+      vec[r] = make_float4(ux * inv, uy * inv, uz * inv, l2);
+    }
+    // nearly opposite partners are possible only when neither family of keys
+    // stays above the cut angle for every cell of the hit (two nearly opposite
+    // vectors cannot both point away from the beam line, or both along the
+    // outer hit's side of z, by more than the cut angle)
+    const bool mirror = team_min<TEAM>(rmin, s_min) <= a.kwin && team_min<TEAM>(zmin, s_min) <= a.kwin;
+    team_sync<TEAM>();
+    if (t < kWave) {  // first positions: a scan over the buckets
+      int carry = 0;
+      for (int b0 = 0; b0 < nb; b0 += kWave) {
+        const int b = b0 + t;
+        const int c = b < nb ? s_bin[b] : 0;
+        const int incl = wave_incl_scan(c);
+        if (b < nb) s_bin[b] = carry + incl - c;
+        carry += __builtin_amdgcn_readlane(incl, kWave - 1);
+      }
+      if (t == 0) s_bin[nb] = carry;
+    }
+    team_sync<TEAM>();
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      if (cell[r] < 0) continue;
+      const int b = place[r] & 0xFF;
+      const int p = s_bin[b] + (place[r] >> 8);
+      s_vec[p] = vec[r];
+      s_x[p] = px[r];
+      s_y[p] = py[r];
+      s_z[p] = pz[r];
+      s_cell[p] = cell[r];
+      s_bk[p] = static_cast<uint8_t>(b);
+    }
+    team_sync<TEAM>();
+    // each cell against the cells of its bucket and the two next to it, and of
+    // the buckets around its negated key (nearly opposite vectors)
+    for (int p = t; p < m; p += TEAM) {
+      const float4 u = s_vec[p];
+      const int b = s_bk[p];
+      bool killed = false;
+      for (int pass = 0; pass < (mirror ? 2 : 1) && !killed; ++pass) {
+        const int c = pass == 0 ? b : nb - 1 - b;
+        int q = s_bin[max(c - 1, 0)];
+        const int q1 = s_bin[min(c + 2, nb)];
+        while (q < q1) {
+          // the next candidates within the cut angle and not longer
+          uint32_t found = 0;
+          for (; q < q1; q += kStep) {
+#pragma unroll
+            for (int k = 0; k < kStep; ++k) {
+              const float4 v = s_vec[q + k];
+              const float d = __builtin_fmaf(u.z, v.z, __builtin_fmaf(u.y, v.y, u.x * v.x));
+              if (!(d * d < a.cos2_min) && !(v.w > u.w)) found |= 1u << k;
+            }
+            found &= (2u << min(q1 - q - 1, kStep - 1)) - 1u;                         // not past the range
+            found &= ~(static_cast<uint32_t>(p - q) < kStep ? 1u << (p - q) : 0u);  // nor itself
+            if (found) break;
+          }
+          const double ux = Xh - double(s_x[p]), uy = Yh - double(s_y[p]), uz = Zh - double(s_z[p]);
+          const double U2 = (ux * ux + uy * uy) + uz * uz;
+          while (found) {
+            const int j = q + __builtin_ctz(found);
+            found &= found - 1;
+            const double vx = Xh - double(s_x[j]), vy = Yh - double(s_y[j]), vz = Zh - double(s_z[j]);
+            killed = kills(ux, uy, uz, U2, vx, vy, vz, (vx * vx + vy * vy) + vz * vz, a.theta2);
+            if (killed) found = 0;
+          }
+          q = killed ? q1 : q + kStep;
+        }
+      }
+      if (killed) a.keep[s_cell[p]] = 0;
+    }
+  }
+}
+
+// The outer hits with more cells than the last tier stages, one work-group each (a
 // persistent grid over the list): the hit's cells are staged in LDS (up to
 // kBigCap; beyond, from global memory) and each thread tests its cells
 // against all the others of the hit whose key is within the cut angle of
@@ -307,10 +384,10 @@ __global__ void __launch_bounds__(kBigBlock) k_fb_kill_big(FbArgs<T> a) {
   __shared__ float s_k[kBigCap];
   __shared__ int32_t s_cell[kBigCap];
   __shared__ int32_t s_start[kBigSegs + 1];
-  const int nbig = *a.n_big;
+  const int nbig = a.n_list[kTiers - 1];
   const float win = a.kwin;
   for (int b = blockIdx.x; b < nbig; b += gridDim.x) {
-    const int h = a.big[b];
+    const int h = a.list[kTiers - 1][b];
     const int sb = a.idx.seg_first[h], ns = a.idx.seg_first[h + 1] - sb;
     const double Xh = double(a.x[h]), Yh = double(a.y[h]), Zh = double(a.z[h]);
     __syncthreads();  // the previous hit's LDS is no longer read
@@ -363,7 +440,7 @@ __global__ void __launch_bounds__(kBigBlock) k_fb_kill_big(FbArgs<T> a) {
         for (int e = threadIdx.x; e < gi.y; e += kBigBlock) {
           const int2 en = a.idx.ent[gi.x + e];
           double ux, uy, uz, U2;
-          vec(a, Xh, Yh, Zh, en.y & kHitMask, ux, uy, uz, U2);
+          vec_to(a, Xh, Yh, Zh, en.y & kHitMask, ux, uy, uz, U2);
           bool killed = false;
           for (int t = 0; t < ns && !killed; ++t) {
             const int2 gj = a.idx.seg[sb + t];
@@ -371,7 +448,7 @@ __global__ void __launch_bounds__(kBigBlock) k_fb_kill_big(FbArgs<T> a) {
               const int2 ej = a.idx.ent[gj.x + f];
               if (ej.x == en.x) continue;
               double vx, vy, vz, V2;
-              vec(a, Xh, Yh, Zh, ej.y & kHitMask, vx, vy, vz, V2);
+              vec_to(a, Xh, Yh, Zh, ej.y & kHitMask, vx, vy, vz, V2);
               killed = kills(ux, uy, uz, U2, vx, vy, vz, V2, a.theta2);
             }
           }
@@ -428,36 +505,33 @@ __global__ void k_fb_set_count(FbArgs<T> a, int32_t* count) {
 template <class T>
 void carve_rest(Carver& c, FbArgs<T>* a, int cap, int n_hits, int32_t** tmp) {
   a->keep = c.take<int32_t>(static_cast<size_t>(cap) + 1);
-  a->mid = c.take<int32_t>(static_cast<size_t>(n_hits));
-  a->n_mid = c.take<int32_t>(1);
-  a->big = c.take<int32_t>(static_cast<size_t>(n_hits));
-  a->n_big = c.take<int32_t>(1);
+  for (int i = 0; i < kTiers; ++i) a->list[i] = c.take<int32_t>(static_cast<size_t>(n_hits));
+  a->n_list = c.take<int32_t>(kTiers);
   a->t_inner = c.take<int32_t>(static_cast<size_t>(cap));
   a->t_outer = c.take<int32_t>(static_cast<size_t>(cap));
   a->t_pair = c.take<uint8_t>(static_cast<size_t>(cap));
   *tmp = c.take<int32_t>(scan_tmp_elems(std::max(cap, n_hits) + 1));
 }
 
-// Work-groups of the listed kernel that are resident at once on this GPU:
-// its grid is persistent, so more would only queue behind the first ones and
-// fewer would leave wavefront slots empty (1536 against 1024 work-groups:
-// 26.5 against 29.1 ms on the PU200 overlap batch).  Looked up once per
-// device and input type, never while a graph is being captured (a plan looks
+// Work-groups of a listed tier's kernel that are resident at once on this
+// GPU: its grid is persistent, so more would only queue behind the first ones
+// and fewer would leave wavefront slots empty.  Looked up once per device,
+// tier and input type, never while a graph is being captured (a plan looks
 // it up when it is created); 1024 when unknown.
 constexpr int kMaxDevices = 64;
 std::mutex g_grid_mu;
-int g_listed_grid[2][kMaxDevices] = {};
+int g_listed_grid[kTiers][2][kMaxDevices] = {};
 
-template <class T>
+template <class T, int TIER>
 int listed_grid() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 1024;
   std::lock_guard<std::mutex> g(g_grid_mu);
-  int& v = g_listed_grid[sizeof(T) == sizeof(double)][dev];
+  int& v = g_listed_grid[TIER][sizeof(T) == sizeof(double)][dev];
   if (v == 0 && !g_capturing) {
     int cus = 0, per = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_fb_kill<T, kCap, 2, true>, 2 * kWave, 0) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_fb_kill<T, TIER>, kTierTeam[TIER], 0) == hipSuccess &&
         cus > 0 && per > 0)
       v = cus * per;
     else
@@ -486,7 +560,10 @@ pt_err run_fishbone(const pt_hits& h, const DevCfg& k, pt_cells& cells, void* ws
     const double win = th >= 1.0 ? 2.0 : std::asin(th) + 1e-5;
     a.nb = static_cast<int32_t>(std::min<double>(kNB, std::max(1.0, std::floor(2.0 / (win * 1.01)))));
     a.kwin = static_cast<float>(win * 1.001);
-    a.phwin = win < 0.9 * kS0 ? static_cast<float>(std::asin(win / kS0) * 1.01 + 1e-5) : 4.f;
+    // a unit vector in single precision is within 4e-7 of the true one in
+    // each component, so a dot product of two within 1e-6 of the cosine and
+    // its square within 2e-6 of the cosine's
+    a.cos2_min = th >= 1.0 ? -1.f : static_cast<float>(1.0 - k.fishbone_theta2 - 4e-6);
   }
   a.count = cells.count;
   a.cap = cap;
@@ -501,11 +578,11 @@ pt_err run_fishbone(const pt_hits& h, const DevCfg& k, pt_cells& cells, void* ws
   carve_rest(c, &a, cap, n_hits, &tmp);
   const int gc = grid_for(cap, kBlock);
   const int gh = grid_for(n_hits + 1, kBlock);
-  PT_HIP_CHECK(fill_i32(a.n_big, 0, 1, s));
-  PT_HIP_CHECK(fill_i32(a.n_mid, 0, 1, s));
+  PT_HIP_CHECK(fill_i32(a.n_list, 0, kTiers, s));
   k_fb_flags<T><<<gc, kBlock, 0, s>>>(a);
-  k_fb_kill<T, kCapSmall, kWaves, false><<<static_cast<unsigned>((n_hits + kWaves - 1) / kWaves), kBlock, 0, s>>>(a);
-  k_fb_kill<T, kCap, 2, true><<<listed_grid<T>(), 2 * kWave, 0, s>>>(a);
+  k_fb_kill<T, 0><<<static_cast<unsigned>(n_hits), kTierTeam[0], 0, s>>>(a);
+  k_fb_kill<T, 1><<<std::min(n_hits, listed_grid<T, 1>()), kTierTeam[1], 0, s>>>(a);
+  k_fb_kill<T, 2><<<std::min(n_hits, listed_grid<T, 2>()), kTierTeam[2], 0, s>>>(a);
   k_fb_kill_big<T><<<256, kBigBlock, 0, s>>>(a);
   PT_LAUNCH_CHECK();
   PT_HIP_CHECK(exclusive_scan_dev(a.keep, cap, cells.count, tmp, s));
@@ -528,8 +605,10 @@ size_t ws_fishbone(int n_hits, int cells_cap) {
 }
 
 void fishbone_prepare() {
-  (void)listed_grid<float>();
-  (void)listed_grid<double>();
+  (void)listed_grid<float, 1>();
+  (void)listed_grid<float, 2>();
+  (void)listed_grid<double, 1>();
+  (void)listed_grid<double, 2>();
 }
 
 pt_err launch_fishbone(const pt_hits& h, const DevCfg& k, pt_cells& cells, void* ws_base, hipStream_t s) {

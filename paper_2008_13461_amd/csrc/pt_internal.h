@@ -158,6 +158,16 @@ inline void clear_stale_error() { (void)hipGetLastError(); }
 // ---------------------------------------------------------------------------
 // device helpers
 
+// Four values of the input type in one vector (one load).
+template <class T>
+struct Vec4Of;
+template <>
+struct Vec4Of<float> { using type = float4; };
+template <>
+struct Vec4Of<double> { using type = double4; };
+template <class T>
+using Vec4 = typename Vec4Of<T>::type;
+
 __device__ inline void status_flag(uint32_t* st, uint32_t bit) {
   if (st) atomicOr(st + PT_ST_FLAGS, bit);
 }
@@ -181,19 +191,32 @@ __device__ inline int wave_sum(int v) {
   for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
   return v;
 }
-__device__ inline float wave_min(float v) {
-#pragma unroll
-  for (int d = kWave / 2; d > 0; d >>= 1) v = fminf(v, __shfl_xor(v, d, kWave));
+// The scans move their partial results with DPP (within rows of 16 lanes,
+// then across rows) instead of through the LDS permute unit, whose latency
+// six dependent steps would pay six times.  A lane without a source combines
+// with `none`.
+template <class F>
+__device__ __forceinline__ int wave_scan_with(int v, int none, F f) {
+  v = f(v, __builtin_amdgcn_update_dpp(none, v, 0x111, 0xf, 0xf, false));  // row_shr:1, 2, 4, 8
+  v = f(v, __builtin_amdgcn_update_dpp(none, v, 0x112, 0xf, 0xf, false));
+  v = f(v, __builtin_amdgcn_update_dpp(none, v, 0x114, 0xf, 0xf, false));
+  v = f(v, __builtin_amdgcn_update_dpp(none, v, 0x118, 0xf, 0xf, false));
+  v = f(v, __builtin_amdgcn_update_dpp(none, v, 0x142, 0xa, 0xf, false));  // row_bcast:15 into rows 1 and 3
+  v = f(v, __builtin_amdgcn_update_dpp(none, v, 0x143, 0xc, 0xf, false));  // row_bcast:31 into rows 2 and 3
   return v;
 }
-__device__ inline int wave_incl_scan(int v) {
-  const int lane = __lane_id();
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int o = __shfl_up(v, d, kWave);
-    if (lane >= d) v += o;
-  }
-  return v;
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  return wave_scan_with(v, 0, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ int wave_max_scan(int v) {
+  return wave_scan_with(v, -0x7fffffff - 1, [](int a, int b) { return max(a, b); });
+}
+// Minimum over the wavefront, the same in every lane.
+__device__ __forceinline__ float wave_min(float v) {
+  const int r = wave_scan_with(__float_as_int(v), __float_as_int(__builtin_inff()), [](int a, int b) {
+    return __float_as_int(fminf(__int_as_float(a), __int_as_float(b)));
+  });
+  return __int_as_float(__builtin_amdgcn_readlane(r, kWave - 1));
 }
 
 // Number of set bits of a wave mask below this lane.

@@ -168,3 +168,39 @@ def test_fishbone_of_outer_hits_with_many_cells():
     ci, co, _ = (t.cpu().numpy() for t in pipe.cells.valid())
     assert doublet_set(ci, co) == doublet_set(ri[keep], ro[keep])
     _inner_index_ok(pipe, h.n_hits)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("theta", [0.01, 0.3])
+def test_fishbone_at_the_edges_of_its_tiers(dtype, theta):
+    """BPix2 hits reached from numbers of BPix1 hits around the ones at which
+    the staging kernel, its rounds of threads and its lists change (64, 256,
+    512, 1024 cells), with wide and narrow key buckets, float and double hits;
+    the kept doublets equal the oracle's."""
+    _need_gpu()
+    from tests.gpu_helpers import run_chain
+    rng = np.random.default_rng(11)
+    counts = [1, 2, 63, 64, 65, 127, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025]
+    xs, ys, zs, ls = [], [], [], []
+    for i, n_in in enumerate(counts):
+        phi_o = -3.0 + 0.4 * i
+        xs.append([6.8 * np.cos(phi_o)]); ys.append([6.8 * np.sin(phi_o)]); zs.append([0.3]); ls.append([1])
+        z = np.repeat(rng.uniform(-4, 4, n_in), 2)[:n_in]          # pairs 1 um apart, and neighbours
+        z[1::2] += 1e-4
+        phi = phi_o + rng.uniform(-0.005, 0.005, n_in)
+        xs.append(2.9 * np.cos(phi)); ys.append(2.9 * np.sin(phi)); zs.append(z); ls.append(np.zeros(n_in))
+    x, y, z = (np.concatenate(a).astype(dtype) for a in (xs, ys, zs))
+    perm = rng.permutation(len(x))
+    layer = np.concatenate(ls).astype(np.uint8)[perm]
+    h = E.Hits(x[perm], y[perm], z[perm], layer, np.zeros(len(x), np.int16), np.full(len(x), -1, np.int32),
+               np.array([0, len(x)], np.int32))
+    cfg = C.default_config(fishbone_theta=theta)
+    ri, ro, _ = O.doublets(cfg, h.x, h.y, h.z, h.layer)
+    per_hit = np.bincount(ro, minlength=len(x))
+    assert sorted(per_hit[per_hit > 0].tolist()) == counts
+    keep = O.fishbone(cfg, h.x, h.y, h.z, ri, ro)
+    assert 0 < keep.sum() < len(keep)
+    pipe, _ = run_chain(h, cfg)
+    ci, co, _ = (t.cpu().numpy() for t in pipe.cells.valid())
+    assert doublet_set(ci, co) == doublet_set(ri[keep], ro[keep])
+    _inner_index_ok(pipe, h.n_hits)
