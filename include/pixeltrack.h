@@ -473,10 +473,11 @@ void pt_plan_destroy(pt_plan plan);
  * "doublets_write", "fishbone" (every kernel of the Fishbone, when it is
  * on), "cell_index" (the index of cells by outer hit), "link_segments"
  * (placing the index segments), "links" (the triplet sweep), "link_emit"
- * (placing the links), "root_count", "root_write", "dfs_count",
- * "dfs_write", "dedup" (several kernels), "fit_fwd" and "fit_bwd" (every
- * kernel of the fit and of its adjoint).  pt_timing_read waits for the
- * recorded events and returns the summed milliseconds and the number of
+ * (placing the links), "root_count" (clearing the search's counters and,
+ * with many cells, counting the roots), "root_write" (listing the roots),
+ * "dfs_count", "dfs_write", "dedup" (the last two several kernels), "fit_fwd"
+ * and "fit_bwd" (every kernel of the fit and of its adjoint).  pt_timing_read
+ * waits for the recorded events and returns the summed milliseconds and the number of
  * launches since the last reset (PT_ERR_ARG when the name has no record). */
 void pt_timing_enable(int32_t on);
 void pt_timing_reset(void);

@@ -40,6 +40,8 @@ struct AmbArgs {
   uint64_t* best_hit;    // [n_hits]
   int32_t* flag;         // [n_max]: 0 dropped, 1 kept, 2 triplet kept by the chi2 rule (pass 1)
   int32_t* pos;          // [n_max + 1]
+  uint64_t* state;       // of the scan of the flags, cleared with the minima
+  int32_t state_words;
 };
 
 __device__ inline int n_tracks(const AmbArgs& a) { return min(*a.count, a.n_max); }
@@ -72,6 +74,7 @@ __device__ inline bool candidate(const AmbArgs& a, int i, int& row, int& nh) {
 
 __global__ void __launch_bounds__(kBlock) k_amb_reset(AmbArgs a) {
   const int n = n_tracks(a);
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < a.state_words; i += gridDim.x * kBlock) a.state[i] = 0;
   for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
     int row, nh;
     if (!candidate(a, i, row, nh)) continue;
@@ -148,7 +151,7 @@ size_t ws_ambiguity(int n_hits, int cells_cap, int n_max) {
   c.take<uint64_t>(static_cast<size_t>(n_hits));
   c.take<int32_t>(static_cast<size_t>(n_max));
   c.take<int32_t>(static_cast<size_t>(n_max) + 1);
-  c.take<int32_t>(scan_tmp_elems(n_max));
+  c.take<uint64_t>(scan_state_words(n_max));
   return c.off + 256;
 }
 
@@ -173,7 +176,8 @@ pt_err launch_ambiguity(const pt_hits& h, const pt_cells& cells, const pt_ntuple
   a.best_hit = c.take<uint64_t>(static_cast<size_t>(h.n_hits));
   a.flag = c.take<int32_t>(static_cast<size_t>(n_max));
   a.pos = c.take<int32_t>(static_cast<size_t>(n_max) + 1);
-  int32_t* tmp = c.take<int32_t>(scan_tmp_elems(n_max));
+  a.state_words = static_cast<int32_t>(scan_state_words(n_max));
+  a.state = c.take<uint64_t>(static_cast<size_t>(a.state_words));
   if (n_max == 0) return fill_i32(n_selected, 0, 1, s) == hipSuccess ? PT_OK : PT_ERR_DEVICE;
   const int g = grid_for(n_max, kBlock, 8192);
   k_amb_reset<<<g, kBlock, 0, s>>>(a);
@@ -181,7 +185,7 @@ pt_err launch_ambiguity(const pt_hits& h, const pt_cells& cells, const pt_ntuple
   k_amb_chi2_rule<<<g, kBlock, 0, s>>>(a);
   k_amb_tip_rule<<<g, kBlock, 0, s>>>(a);
   PT_LAUNCH_CHECK();
-  PT_HIP_CHECK(exclusive_scan_to(a.flag, a.pos, n_max, a.count, n_selected, tmp, s));
+  PT_HIP_CHECK(exclusive_scan(a.flag, a.pos, n_max, a.count, ScanTotal{n_selected}, a.state, s));
   k_amb_list<<<g, kBlock, 0, s>>>(a, selected);
   PT_LAUNCH_CHECK();
   return PT_OK;

@@ -179,7 +179,7 @@ size_t pt_workspace_size(const pt_config* cfg, int32_t n_hits, int32_t n_events,
   if (!cfg || n_hits < 0 || n_events < 0 || cells_cap < 0 || tuplets_cap < 0) return 0;
   DevCfg d;
   if (!derive_config(*cfg, &d)) return 0;
-  size_t s = ws_doublets(n_hits, n_events, d.n_bins);
+  size_t s = ws_doublets(n_hits, n_events, d.n_bins, d.fishbone_theta2 > 0.0 ? cells_cap : 0);
   if (d.fishbone_theta2 > 0.0) s = std::max(s, ws_fishbone(n_hits, cells_cap));
   s = std::max(s, ws_links(n_hits, cells_cap));
   s = std::max(s, ws_ntuplets(cells_cap, tuplets_cap));
@@ -196,7 +196,7 @@ pt_err pt_build_doublets(const pt_hits* hits, const pt_config* cfg, pt_cells* ce
   if (cells->cap < 0 || !cells->count || (hits->n_hits > 0 && (!cells->inner_first || !cells->inner_count)))
     return PT_ERR_ARG;
   if (cells->cap > 0 && (!cells->inner || !cells->outer || !cells->pair)) return PT_ERR_ARG;
-  size_t need = ws_doublets(hits->n_hits, hits->n_events, d.n_bins);
+  size_t need = ws_doublets(hits->n_hits, hits->n_events, d.n_bins, d.fishbone_theta2 > 0.0 ? cells->cap : 0);
   if (d.fishbone_theta2 > 0.0) need = std::max(need, ws_fishbone(hits->n_hits, cells->cap));
   if (!ws_ok(ws, need)) return PT_ERR_WORKSPACE;
   clear_stale_error();

@@ -21,8 +21,6 @@
 
 namespace pt {
 
-pt_err launch_fishbone(const pt_hits& h, const DevCfg& k, pt_cells& cells, void* ws_base, hipStream_t s);
-
 // The cut predicates of Table 1, as documented in pixeltrack.h (tdphi is
 // tan_dphi of the pair, loaded once per pair by the caller).  ALL: PhiW,
 // ZIP and PT are all on, and the three are evaluated without branches (a
@@ -168,6 +166,7 @@ template <class T>
 struct DoubletArgs {
   int32_t n_hits;
   const int32_t* bin_start;
+  const int32_t* valid;    // number of sorted (valid) hits
   const int32_t* skey;
   const int32_t* sorted_hit;
   const Vec4<T>* sP;  // sorted (x, y, z, 0) in the input type: one 16-byte load for float hits
@@ -251,7 +250,7 @@ __global__ void __launch_bounds__(WAVES * kWave) k_doublets(DevCfg k, DoubletArg
   const int last = WRITE ? a.off[j + 1] : 0;
   const int hit_i = WRITE ? a.sorted_hit[j] : 0;
   const int nst = WRITE ? a.n_chunks[j] : 0;
-  const int total = a.bin_start[-1];  // valid (sorted) hits
+  const int total = *a.valid;
   if (j >= total) {
     if (!WRITE && lane == 0) {
       a.cnt[j] = 0;
@@ -385,35 +384,30 @@ __global__ void __launch_bounds__(WAVES * kWave) k_doublets(DevCfg k, DoubletArg
   }
 }
 
-__global__ void k_finish_cells(const int32_t* total, int32_t cap, int32_t* count, uint32_t* status) {
-  const int t = *total;
-  *count = t;
-  if (t > cap) status_flag(status, PT_FLAG_CELLS_OVERFLOW);
-}
-
-// bin_start is laid out with one leading word that receives the number of
-// valid hits, so that kernels can read it as bin_start[-1].
-__global__ void k_copy_total(const int32_t* __restrict__ bin_start, int nb, int32_t* __restrict__ dst) {
-  *dst = bin_start[nb];
-}
-
 }  // namespace
 
-size_t ws_doublets(int n_hits, int n_events, int n_bins) {
+// Words cleared before the hits are counted: the states of the two scans and
+// the counts of the bins.
+static size_t bin_words(int64_t nb, int n_hits) {
+  return 2 * (scan_state_words(nb) + scan_state_words(n_hits)) + static_cast<size_t>(nb);
+}
+
+size_t ws_doublets(int n_hits, int n_events, int n_bins, int raw_cells) {
   const size_t nb = static_cast<size_t>(n_events) * kLayers * n_bins;
   Carver c(nullptr);
+  if (raw_cells > 0) (void)carve_raw_cells(c, pt_cells{}, raw_cells);
   c.take<int32_t>(n_hits);        // key
   c.take<int32_t>(n_hits);        // rank
-  c.take<int32_t>(nb + 2);        // [total] + bin counts/starts (+ end)
+  c.take<int32_t>(bin_words(nb, n_hits));  // scan states, bin counts
+  c.take<int32_t>(nb + 1);        // bin starts (+ end)
   c.take<int32_t>(n_hits);        // sorted_hit
   c.take<int32_t>(n_hits);        // skey
   c.take<double4>(n_hits);        // sP (x, y, z) in the input type: at most 32 bytes
   c.take<double>(n_hits);         // sR
-  c.take<int32_t>(n_hits + 1);    // cnt / off
+  c.take<int32_t>(n_hits);        // cnt
+  c.take<int32_t>(static_cast<size_t>(n_hits) + 1);  // off
   c.take<int4>(static_cast<size_t>(n_hits) * kMaskChunks);  // kept groups of candidates
   c.take<int32_t>(n_hits);        // groups per hit
-  const size_t t = scan_tmp_elems(std::max<int64_t>(static_cast<int64_t>(nb), n_hits));
-  c.take<int32_t>(t);
   return c.off + 256;
 }
 
@@ -450,53 +444,58 @@ static pt_err run_doublets(const pt_hits& h, const DevCfg& k, pt_cells& cells, u
   const int B = k.n_bins;
   const int64_t nb = static_cast<int64_t>(h.n_events) * kLayers * B;
   Carver c(ws.ptr);
+  // with the Fishbone the cells go to the workspace, and from there to the output
+  const bool fishbone = k.fishbone_theta2 > 0.0 && n > 0 && cells.cap > 0;
+  pt_cells raw = cells;
+  if (fishbone) raw = carve_raw_cells(c, cells, cells.cap);
+  const Carver behind = c;
   int32_t* key = c.take<int32_t>(n);
   int32_t* rank = c.take<int32_t>(n);
-  int32_t* bins = c.take<int32_t>(nb + 2);   // bins[0] = valid hits; bins+1 = counts -> starts
+  int32_t* bins = c.take<int32_t>(bin_words(nb, n));
+  int32_t* bin_start = c.take<int32_t>(nb + 1);
   int32_t* sorted_hit = c.take<int32_t>(n);
   int32_t* skey = c.take<int32_t>(n);
   Vec4<T>* sP = c.take<Vec4<T>>(n);
   double* sR = c.take<double>(n);
-  int32_t* cnt = c.take<int32_t>(n + 1);
+  int32_t* cnt = c.take<int32_t>(n);
+  int32_t* off = c.take<int32_t>(static_cast<size_t>(n) + 1);
   int4* chunks = c.take<int4>(static_cast<size_t>(n) * kMaskChunks);
   int32_t* n_chunks = c.take<int32_t>(n);
-  int32_t* tmp = c.take<int32_t>(scan_tmp_elems(std::max<int64_t>(nb, n)));
-  int32_t* bin_start = bins + 1;
+  uint64_t* bin_state = reinterpret_cast<uint64_t*>(bins);
+  uint64_t* cnt_state = bin_state + scan_state_words(nb);
+  int32_t* bin_count = reinterpret_cast<int32_t*>(cnt_state + scan_state_words(n));
+  const int32_t* valid = bin_start + nb;  // the scan's total
 
   HitsIn<T> in{n, h.n_events, h.event_offsets, static_cast<const T*>(h.x), static_cast<const T*>(h.y),
                static_cast<const T*>(h.z), h.layer};
-  PT_HIP_CHECK(fill_i32(bins, 0, nb + 2, s));
-  k_hit_keys<T><<<grid_for(n, 256), 256, 0, s>>>(in, B, k.bin_scale, key, rank, bin_start, status);
+  PT_HIP_CHECK(fill_i32(bins, 0, static_cast<int64_t>(bin_words(nb, n)), s));
+  k_hit_keys<T><<<grid_for(n, 256), 256, 0, s>>>(in, B, k.bin_scale, key, rank, bin_count, status);
   PT_LAUNCH_CHECK();
-  PT_HIP_CHECK(exclusive_scan(bin_start, nb, tmp, s));
-  k_copy_total<<<1, 1, 0, s>>>(bin_start, static_cast<int>(nb), bins);
-  PT_LAUNCH_CHECK();
+  PT_HIP_CHECK(exclusive_scan(bin_count, bin_start, nb, nullptr, ScanTotal{}, bin_state, s));
   // the hits in arrival order within their bins, then each bin ordered by
   // hit index
   int32_t* arrived = cnt;  // the per-hit counts are free until the count pass
   k_scatter<T><<<grid_for(n, 256), 256, 0, s>>>(in, key, rank, bin_start, arrived, skey, cells.inner_count);
   PT_LAUNCH_CHECK();
-  k_bin_order<T><<<grid_for(n, 256), 256, 0, s>>>(in, bins, bin_start, arrived, skey, sorted_hit, sP, sR);
+  k_bin_order<T><<<grid_for(n, 256), 256, 0, s>>>(in, valid, bin_start, arrived, skey, sorted_hit, sP, sR);
   PT_LAUNCH_CHECK();
 
-  DoubletArgs<T> a{n, bin_start, skey, sorted_hit, sP, sR, cnt, cnt, chunks, n_chunks, cells.cap, cells.inner,
-                cells.outer, cells.pair, cells.inner_first, cells.inner_count};
-  // bin_start[-1] holds the number of valid hits (sorted positions).
+  DoubletArgs<T> a{n, bin_start, valid, skey, sorted_hit, sP, sR, cnt, off, chunks, n_chunks, raw.cap, raw.inner,
+                   raw.outer, raw.pair, raw.inner_first, raw.inner_count};
   const int block = (k.block_doublets == 64 || k.block_doublets == 128 || k.block_doublets == 512)
                         ? k.block_doublets : 256;
   void* tok = timing_begin(s);
   launch_doublets<false, T>(k, a, n, block, s);
   timing_end(tok, "doublets_count", s);
   PT_LAUNCH_CHECK();
-  PT_HIP_CHECK(exclusive_scan(cnt, n, tmp, s));
+  PT_HIP_CHECK(exclusive_scan(cnt, off, n, nullptr, ScanTotal{raw.count, raw.cap, PT_FLAG_CELLS_OVERFLOW, status}, cnt_state,
+                              s));
   tok = timing_begin(s);
   launch_doublets<true, T>(k, a, n, kWriteBlock, s);
   timing_end(tok, "doublets_write", s);
   PT_LAUNCH_CHECK();
-  k_finish_cells<<<1, 1, 0, s>>>(cnt + n, cells.cap, cells.count, status);
-  PT_LAUNCH_CHECK();
-  // the Fishbone reuses the workspace from its start (the sorted hits are dead)
-  if (k.fishbone_theta2 > 0.0) return launch_fishbone(h, k, cells, ws.ptr, s);
+  // the Fishbone reuses the workspace behind the cells (the sorted hits are dead)
+  if (fishbone) return launch_fishbone(h, k, raw, cells, behind, s);
   return PT_OK;
 }
 

@@ -2,7 +2,8 @@
 // hit, the longer of two aligned ones is dropped, so that the overlapping
 // modules of a layer give one n-tuplet per particle instead of several.
 //
-// Runs inside pt_build_doublets after the write pass when the Fishbone is on:
+// Runs inside pt_build_doublets when the Fishbone is on; the doublet step then
+// writes its cells to the workspace:
 //   1. the stored cells are indexed by outer hit with the index of the link
 //      step (blocks of consecutive cells grouped by outer hit in LDS, one
 //      segment per block and hit; no per-cell atomic);
@@ -14,9 +15,9 @@
 //      in single precision filters the pairs, the exact test, in double,
 //      decides and clears the cell's keep flag.  Hits with more cells than a
 //      team stages are listed for the next larger one;
-//   3. the kept cells are compacted in their order (a scan of the flags),
-//      through a copy in the workspace, and each inner hit's range of cells
-//      is moved with them.
+//   3. the kept cells are written to the output in their order, in one pass
+//      over the flags (the sum of the tiles before comes with it), and each
+//      inner hit's range of cells is moved with them.
 // The test is the one of pixeltrack.h, in double, as parenthesised, without
 // contraction, from the hits' coordinates promoted to double.
 #include <algorithm>
@@ -47,28 +48,32 @@ struct FbArgs {
   int32_t nb;             // key buckets: each at least the cut angle wide
   float kwin;             // key window: asin(theta) with a margin, 2 when theta >= 1
   float cos2_min;         // squared cosine, in single precision, below which two vectors are not aligned
-  const int32_t* count;   // cells found
+  const int32_t* found;   // cells found
   int32_t cap;
-  int32_t* inner;
-  int32_t* outer;
-  uint8_t* pair;
+  const int32_t* inner;   // the cells as found
+  const int32_t* outer;
+  const uint8_t* pair;
   int32_t* inner_first;
   int32_t* inner_count;
   OuterIndex idx;
   // workspace
-  int32_t* keep;          // [cap + 1] flags, then positions
+  uint8_t* keep;          // [cap, a multiple of 16] flags
+  int32_t* before;        // [cap / 16] kept cells before each group of 16
   int32_t* list[kTiers];  // [n_hits] outer hits with more cells than tier i stages
   int32_t* n_list;        // [kTiers] how many
-  int32_t* t_inner;       // [cap] compacted copies
-  int32_t* t_outer;
-  uint8_t* t_pair;
+  int32_t* out_inner;     // the output cells
+  int32_t* out_outer;
+  uint8_t* out_pair;
+  int32_t* out_count;
+  uint64_t* state;        // of the scan of the flags
+  int32_t state_words;
 };
 
 // Cells the Fishbone works on: every stored cell, or none when the cells
 // overflowed their capacity (the products are truncated anyway).
 template <class T>
 __device__ inline int stored(const FbArgs<T>& a) {
-  const int c = *a.count;
+  const int c = *a.found;
   return c <= a.cap ? c : 0;
 }
 
@@ -110,8 +115,12 @@ __device__ inline void vec_to(const FbArgs<T>& a, double Xh, double Yh, double Z
 
 template <class T>
 __global__ void k_fb_flags(FbArgs<T> a) {
-  const int n = stored(a);
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) a.keep[c] = 1;
+  const int n = min(*a.found, a.cap);
+  const int first = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  for (int64_t c = first; 16 * c < n; c += step)
+    reinterpret_cast<int4*>(a.keep)[c] = make_int4(0x01010101, 0x01010101, 0x01010101, 0x01010101);
+  for (int i = first; i < a.state_words; i += step) a.state[i] = 0;
+  if (first < kTiers) a.n_list[first] = 0;
 }
 
 // Barrier and reductions over the TEAM threads (a wavefront, or the whole
@@ -459,58 +468,114 @@ __global__ void __launch_bounds__(kBigBlock) k_fb_kill_big(FbArgs<T> a) {
   }
 }
 
+// The 16 flags of cells 16 g .. 16 g + 15 below n as a bit mask.
 template <class T>
-__global__ void k_fb_scatter(FbArgs<T> a) {
-  const int n = stored(a);
-  const int32_t* pos = a.keep;  // scanned
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) {
-    const int p = pos[c];
-    if (pos[c + 1] == p) continue;  // dropped
-    a.t_inner[p] = a.inner[c];
-    a.t_outer[p] = a.outer[c];
-    a.t_pair[p] = a.pair[c];
-  }
+__device__ inline uint32_t flags16(const FbArgs<T>& a, int64_t g, int n) {
+  const int left = n - static_cast<int>(16 * g);
+  if (left <= 0) return 0;
+  const int4 q = reinterpret_cast<const int4*>(a.keep)[g];
+  const uint32_t w[4] = {static_cast<uint32_t>(q.x), static_cast<uint32_t>(q.y), static_cast<uint32_t>(q.z),
+                         static_cast<uint32_t>(q.w)};
+  uint32_t m = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) m |= ((w[k] * 0x10204080u) >> 28) << (4 * k);  // byte b's bit 0 to bit b
+  return left < 16 ? m & ((1u << left) - 1u) : m;
 }
 
-// Copies the compacted cells back and moves each inner hit's range.
+// Writes the kept cells to the output in their order, one tile of kTileItems
+// cells per work-group, and the kept cells before each 16 for the ranges.
+// One thread's 16 flags give the positions of 16 consecutive cells; the cells
+// themselves go one per thread and round, through LDS, so that loads and
+// stores stay coalesced.
 template <class T>
-__global__ void k_fb_copy_back(FbArgs<T> a) {
+__global__ void __launch_bounds__(kTileThreads) k_fb_compact(FbArgs<T> a) {
+  static_assert(kScanItems == 16, "a thread's flags are one 16-byte vector");
+  __shared__ int32_t s_wave[kTileThreads / kWave + 1];
+  __shared__ int32_t s_at[kTileThreads];    // per 16 cells: kept ones before
+  __shared__ uint32_t s_m[kTileThreads];    // ... and their flags
+  const int found = *a.found;
+  const int n = min(found, a.cap);
+  const int tiles = n > 0 ? (n + kTileItems - 1) / kTileItems : 1;
+  const int tile = blockIdx.x;
+  if (tile >= tiles) return;
+  const int t = threadIdx.x;
+  const int64_t g0 = static_cast<int64_t>(tile) * kTileThreads;
+  const uint32_t m = flags16(a, g0 + t, n);
+  int end;
+  const int at = tile_exclusive(__popc(m), tiles > 1 ? a.state : nullptr, tile, s_wave, &end, [&](int i) {
+    int x = 0;  // a tile before this one is full
+    for (int q = __lane_id(); q < kTileThreads; q += kWave)
+      x += __popc(flags16(a, static_cast<int64_t>(i) * kTileThreads + q, n));
+    return wave_sum(x);
+  });
+  s_at[t] = at;
+  s_m[t] = m;
+  if (16 * (g0 + t) < n) a.before[g0 + t] = at;
+  __syncthreads();
+  constexpr int kBatch = 4;
+  for (int r = 0; r < kScanItems; r += kBatch) {
+    int in[kBatch], out[kBatch], to[kBatch];
+    uint8_t pr[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int c = (r + u) * kTileThreads + t;  // cell of the tile
+      const uint32_t f = s_m[c >> 4];
+      to[u] = (f >> (c & 15)) & 1u ? s_at[c >> 4] + __popc(f & ((1u << (c & 15)) - 1u)) : -1;
+      const int64_t cell = 16 * g0 + c;
+      if (to[u] >= 0) {
+        in[u] = a.inner[cell];
+        out[u] = a.outer[cell];
+        pr[u] = a.pair[cell];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      if (to[u] < 0) continue;
+      a.out_inner[to[u]] = in[u];
+      a.out_outer[to[u]] = out[u];
+      a.out_pair[to[u]] = pr[u];
+    }
+  }
+  if (tile == tiles - 1 && t == 0) *a.out_count = found > a.cap ? found : end;
+}
+
+// Moves each inner hit's range of cells with them (unless they overflowed), and
+// leaves the cells as found in the places of the output past the kept ones.
+template <class T>
+__global__ void k_fb_ranges(FbArgs<T> a) {
   const int n = stored(a);
   if (n == 0) return;
-  const int32_t* pos = a.keep;
-  const int total = pos[n];
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < total; p += gridDim.x * blockDim.x) {
-    a.inner[p] = a.t_inner[p];
-    a.outer[p] = a.t_outer[p];
-    a.pair[p] = a.t_pair[p];
-  }
-  for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < a.n_hits; h += gridDim.x * blockDim.x) {
+  auto kept_before = [&](int c) {  // c in [0, n]
+    const int g = (c < n ? c : n - 1) >> 4;
+    return a.before[g] + __popc(flags16(a, g, n) & ((1u << (c - 16 * g)) - 1u));
+  };
+  const int first = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  for (int h = first; h < a.n_hits; h += step) {
     const int cnt = a.inner_count[h];
     if (cnt <= 0) continue;
     const int f = a.inner_first[h];
-    const int e = min(f + cnt, n);
-    a.inner_first[h] = pos[min(f, n)];
-    a.inner_count[h] = pos[e] - pos[min(f, n)];
+    const int p = kept_before(f);
+    a.inner_first[h] = p;
+    a.inner_count[h] = kept_before(f + cnt) - p;
+  }
+  for (int c = kept_before(n) + first; c < n; c += step) {
+    a.out_inner[c] = a.inner[c];
+    a.out_outer[c] = a.outer[c];
+    a.out_pair[c] = a.pair[c];
   }
 }
 
-// The new number of cells (a kernel of its own: the others read the old one).
+// Workspace after the cells as found and the outer-hit index: flags, lists,
+// states.
 template <class T>
-__global__ void k_fb_set_count(FbArgs<T> a, int32_t* count) {
-  const int n = stored(a);
-  if (n > 0) *count = a.keep[n];
-}
-
-// Workspace after the outer-hit index: the flags, the copies, the scan's.
-template <class T>
-void carve_rest(Carver& c, FbArgs<T>* a, int cap, int n_hits, int32_t** tmp) {
-  a->keep = c.take<int32_t>(static_cast<size_t>(cap) + 1);
+void carve_rest(Carver& c, FbArgs<T>* a, int cap, int n_hits) {
+  const size_t groups = (static_cast<size_t>(cap) + 15) / 16;
+  a->keep = c.take<uint8_t>(16 * groups);
+  a->before = c.take<int32_t>(groups);
   for (int i = 0; i < kTiers; ++i) a->list[i] = c.take<int32_t>(static_cast<size_t>(n_hits));
   a->n_list = c.take<int32_t>(kTiers);
-  a->t_inner = c.take<int32_t>(static_cast<size_t>(cap));
-  a->t_outer = c.take<int32_t>(static_cast<size_t>(cap));
-  a->t_pair = c.take<uint8_t>(static_cast<size_t>(cap));
-  *tmp = c.take<int32_t>(scan_tmp_elems(std::max(cap, n_hits) + 1));
+  a->state_words = static_cast<int32_t>(scan_state_words(cap));
+  a->state = c.take<uint64_t>(static_cast<size_t>(a->state_words));
 }
 
 // Work-groups of a listed tier's kernel that are resident at once on this
@@ -541,11 +606,9 @@ int listed_grid() {
 }
 
 template <class T>
-pt_err run_fishbone(const pt_hits& h, const DevCfg& k, pt_cells& cells, void* ws_base, hipStream_t s) {
+pt_err run_fishbone(const pt_hits& h, const DevCfg& k, const pt_cells& raw, pt_cells& cells, Carver c, hipStream_t s) {
   const int n_hits = h.n_hits;
   const int cap = cells.cap;
-  if (n_hits == 0 || cap == 0) return PT_OK;
-  Carver c(ws_base);
   FbArgs<T> a{};
   a.x = static_cast<const T*>(h.x);
   a.y = static_cast<const T*>(h.y);
@@ -565,30 +628,28 @@ pt_err run_fishbone(const pt_hits& h, const DevCfg& k, pt_cells& cells, void* ws
     // its square within 2e-6 of the cosine's
     a.cos2_min = th >= 1.0 ? -1.f : static_cast<float>(1.0 - k.fishbone_theta2 - 4e-6);
   }
-  a.count = cells.count;
+  a.found = raw.count;
   a.cap = cap;
-  a.inner = cells.inner;
-  a.outer = cells.outer;
-  a.pair = cells.pair;
+  a.inner = raw.inner;
+  a.outer = raw.outer;
+  a.pair = raw.pair;
   a.inner_first = cells.inner_first;
   a.inner_count = cells.inner_count;
-  const pt_err e = build_outer_index(h, cells, c, a.idx, s);
+  a.out_inner = cells.inner;
+  a.out_outer = cells.outer;
+  a.out_pair = cells.pair;
+  a.out_count = cells.count;
+  const pt_err e = build_outer_index(h, raw, c, a.idx, s);
   if (e != PT_OK) return e;
-  int32_t* tmp = nullptr;
-  carve_rest(c, &a, cap, n_hits, &tmp);
-  const int gc = grid_for(cap, kBlock);
-  const int gh = grid_for(n_hits + 1, kBlock);
-  PT_HIP_CHECK(fill_i32(a.n_list, 0, kTiers, s));
-  k_fb_flags<T><<<gc, kBlock, 0, s>>>(a);
+  carve_rest(c, &a, cap, n_hits);
+  k_fb_flags<T><<<grid_for(std::max(cap / 16 + 1, a.state_words), kBlock), kBlock, 0, s>>>(a);
   k_fb_kill<T, 0><<<static_cast<unsigned>(n_hits), kTierTeam[0], 0, s>>>(a);
   k_fb_kill<T, 1><<<std::min(n_hits, listed_grid<T, 1>()), kTierTeam[1], 0, s>>>(a);
   k_fb_kill<T, 2><<<std::min(n_hits, listed_grid<T, 2>()), kTierTeam[2], 0, s>>>(a);
   k_fb_kill_big<T><<<256, kBigBlock, 0, s>>>(a);
   PT_LAUNCH_CHECK();
-  PT_HIP_CHECK(exclusive_scan_dev(a.keep, cap, cells.count, tmp, s));
-  k_fb_scatter<T><<<gc, kBlock, 0, s>>>(a);
-  k_fb_copy_back<T><<<std::max(gc, gh), kBlock, 0, s>>>(a);
-  k_fb_set_count<T><<<1, 1, 0, s>>>(a, cells.count);
+  k_fb_compact<T><<<static_cast<unsigned>(tiles_of(cap, kTileItems)), kTileThreads, 0, s>>>(a);
+  k_fb_ranges<T><<<grid_for(std::max(n_hits, cap / 8), kBlock), kBlock, 0, s>>>(a);
   PT_LAUNCH_CHECK();
   return PT_OK;
 }
@@ -597,11 +658,20 @@ pt_err run_fishbone(const pt_hits& h, const DevCfg& k, pt_cells& cells, void* ws
 
 size_t ws_fishbone(int n_hits, int cells_cap) {
   Carver c(nullptr);
-  c.off = ws_outer_index(n_hits, cells_cap);
+  (void)carve_raw_cells(c, pt_cells{}, cells_cap);
+  c.off += ws_outer_index(n_hits, cells_cap);
   FbArgs<float> a{};
-  int32_t* tmp = nullptr;
-  carve_rest(c, &a, cells_cap, n_hits, &tmp);
-  return c.off + 256;
+  carve_rest(c, &a, cells_cap, n_hits);
+  return c.off + 512;
+}
+
+pt_cells carve_raw_cells(Carver& c, const pt_cells& cells, int cells_cap) {
+  pt_cells raw = cells;
+  raw.inner = c.take<int32_t>(static_cast<size_t>(cells_cap));
+  raw.outer = c.take<int32_t>(static_cast<size_t>(cells_cap));
+  raw.pair = c.take<uint8_t>(static_cast<size_t>(cells_cap));
+  raw.count = c.take<int32_t>(1);
+  return raw;
 }
 
 void fishbone_prepare() {
@@ -611,10 +681,11 @@ void fishbone_prepare() {
   (void)listed_grid<double, 2>();
 }
 
-pt_err launch_fishbone(const pt_hits& h, const DevCfg& k, pt_cells& cells, void* ws_base, hipStream_t s) {
+pt_err launch_fishbone(const pt_hits& h, const DevCfg& k, const pt_cells& raw, pt_cells& cells, Carver c,
+                       hipStream_t s) {
   void* tok = timing_begin(s);
-  const pt_err e = h.dtype == PT_F64 ? run_fishbone<double>(h, k, cells, ws_base, s)
-                                     : run_fishbone<float>(h, k, cells, ws_base, s);
+  const pt_err e = h.dtype == PT_F64 ? run_fishbone<double>(h, k, raw, cells, c, s)
+                                     : run_fishbone<float>(h, k, raw, cells, c, s);
   timing_end(tok, "fishbone", s);
   return e;
 }

@@ -13,7 +13,7 @@
 //     layer pair.
 //  2. k_cell_index: each chunk of cells is grouped by outer hit in an LDS
 //     hash table and written to the index grouped that way.
-//  3. exclusive scan of the per-hit segment counts, then k_seg_scatter:
+//  3. an exclusive scan of the per-hit segment counts, then k_seg_scatter:
 //     each hit's in-cells as a list of segments of the index (8 bytes per
 //     cell: cell, inner hit), one segment per chunk of k_cell_index.
 //  4. k_link_hits: one wavefront per middle hit.  Lanes hold the in-cells.
@@ -32,10 +32,9 @@
 //     gained an inner link are flagged (has_inner) in one coalesced run.
 //  5. the counts are recorded straight into out_count; their scan into
 //     out_start places every in-cell's links, in cell order (no shared
-//     counter: same-address atomics serialise): after a scan of the counts'
-//     tile sums, k_link_place scans each tile, writes out_start and the
-//     links of the cells with at most kLocal, and k_links_overflow
-//     recomputes the few in-cells with more.
+//     counter: same-address atomics serialise): k_link_place scans them tile
+//     by tile, writes out_start and the links of the cells with at most
+//     kLocal, and k_links_overflow recomputes the few in-cells with more.
 #include "pt_internal.h"
 
 #include <algorithm>
@@ -124,14 +123,20 @@ __device__ __forceinline__ bool beam_pass(double X0, double Y0, double X1, doubl
 }
 
 // Hit table: (X, Y, Z, R) in double, one 32-byte entry per hit, R = sqrt(X X + Y Y).
+// Also clears what the later kernels of the step count in: the hits' segment
+// counts and `words` scratch words.
 template <class T>
 __global__ void k_hit_table(int n, const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ z,
-                            double4* __restrict__ hx) {
-  for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < n; h += gridDim.x * blockDim.x) {
+                            double4* __restrict__ hx, int32_t* __restrict__ n_seg, uint64_t* __restrict__ scratch,
+                            int words) {
+  const int first = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  for (int h = first; h < n; h += step) {
     const double X = static_cast<double>(x[h]);
     const double Y = static_cast<double>(y[h]);
     hx[h] = make_double4(X, Y, static_cast<double>(z[h]), sqrt(X * X + Y * Y));
+    n_seg[h] = 0;
   }
+  for (int i = first; i < words; i += step) scratch[i] = 0;
 }
 
 struct IndexArgs {
@@ -143,7 +148,7 @@ struct IndexArgs {
   InCell* ent;         // the block's cells grouped by outer hit, in the block's own range
   int4* grp;           // per block: its groups (outer hit, first entry, cells, slot in the hit's list)
   int32_t* n_grp;      // per block: number of groups
-  int32_t* n_seg;      // [n_hits + 1] groups ending on each hit
+  int32_t* n_seg;      // [n_hits] groups ending on each hit
   int32_t* out_count;  // cleared here (link counts of the cells)
   uint8_t* has_inner;
 };
@@ -853,94 +858,67 @@ __device__ __forceinline__ void emit_cell(const EmitArgs& a, int c, int cnt, int
   }
 }
 
-// Places the links: each block takes one tile of kScanTile cells, scans
-// their link counts (the tile's offset comes from the scan of the tile sums)
-// into out_start, and writes the links of its cells with 1..kLocal of them
-// from their records.  Cells with more than kLocal links are written by
-// k_links_overflow.  The counts are read once, the positions never read
-// back: each thread scans kEmitItems consecutive counts (16-byte vectors),
-// the positions go through LDS (a count is the difference of two), and the
-// records are then taken one cell per thread and round, consecutive cells
-// on consecutive lanes.
-constexpr int kEmitBlock = 256;
-constexpr int kEmitItems = kScanTile / kEmitBlock;
-static_assert(kEmitItems % 4 == 0, "counts are read as 16-byte vectors");
-
-__global__ void __launch_bounds__(kEmitBlock) k_link_place(EmitArgs a, const int32_t* __restrict__ tile_off,
-                                                          int32_t* __restrict__ out_start, int32_t* __restrict__ total) {
-  __shared__ int32_t s_pos[kScanTile + 1];  // positions; a cell's count is the difference to the next
-  __shared__ int32_t s_wave[kEmitBlock / kWave + 1];
-  if (blockIdx.x == 0 && threadIdx.x == 0) *total = tile_off[gridDim.x];
+// Places the links: each work-group takes one tile of kTileItems cells, scans
+// their link counts into out_start (the sum of the tiles before comes from
+// tile_off when OFF, else from the tiles' states), and writes the links of
+// its cells with 1..kLocal of them from their records.  Cells with more than
+// kLocal links are written by k_links_overflow.  Each thread scans kScanItems
+// consecutive counts (16-byte vectors when VEC), the positions go through LDS
+// (a count is the difference of two), and the records are then taken one cell
+// per thread and round, consecutive cells on consecutive lanes.  The last tile
+// writes the total.
+template <bool VEC, bool OFF>
+__global__ void __launch_bounds__(kTileThreads) k_link_place(EmitArgs a, uint64_t* state,
+                                                            const int32_t* __restrict__ tile_off,
+                                                            int32_t* __restrict__ out_start, int32_t* __restrict__ total,
+                                                            uint32_t* status) {
+  __shared__ int32_t s_pos[kTileItems + 1];  // positions; a cell's count is the difference to the next
+  __shared__ int32_t s_wave[kTileThreads / kWave + 1];
   const int n = min(*a.cell_count, a.cells_cap);
-  const int64_t first = static_cast<int64_t>(blockIdx.x) * kScanTile;
-  if (first >= n) return;
-  const int m = static_cast<int>(min<int64_t>(kScanTile, n - first));  // cells of this tile
+  const int tiles = n > 0 ? (n + kTileItems - 1) / kTileItems : 1;
+  const int tile = blockIdx.x;
+  if (tile >= tiles) return;
   const int t = threadIdx.x;
-  const int lane = __lane_id(), wave = t / kWave;
-  // the counts of cells t * kEmitItems .. + kEmitItems of the tile
-  int v[kEmitItems];
-  const int at = t * kEmitItems;
-  const bool vec = m == kScanTile && reinterpret_cast<uintptr_t>(a.out_count) % 16 == 0 &&
-                   reinterpret_cast<uintptr_t>(out_start) % 16 == 0;
-  if (vec) {
-    const int4* p = reinterpret_cast<const int4*>(a.out_count + first + at);
-#pragma unroll
-    for (int i = 0; i < kEmitItems / 4; ++i) {
-      const int4 q = p[i];
-      v[4 * i] = q.x;
-      v[4 * i + 1] = q.y;
-      v[4 * i + 2] = q.z;
-      v[4 * i + 3] = q.w;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < kEmitItems; ++i) v[i] = at + i < m ? a.out_count[first + at + i] : 0;
-  }
-  // exclusive prefix of the thread sums over the block
+  const int64_t first = static_cast<int64_t>(tile) * kTileItems;
+  const int m = static_cast<int>(min<int64_t>(kTileItems, n - first));  // cells of this tile
+  // the counts of cells t * kScanItems .. + kScanItems of the tile
+  const int at = t * kScanItems;
+  int v[kScanItems];
+  load_items<VEC>(a.out_count, first + at, n, v);
+  const int off = OFF ? tile_off[tile] : 0;
   int sum = 0;
 #pragma unroll
-  for (int i = 0; i < kEmitItems; ++i) sum += v[i];
-  const int incl = wave_incl_scan(sum);
-  if (lane == kWave - 1) s_wave[wave] = incl;
-  __syncthreads();
-  if (t == 0) {
-    int run = 0;
-    for (int w = 0; w < kEmitBlock / kWave; ++w) {
-      const int c = s_wave[w];
-      s_wave[w] = run;
-      run += c;
-    }
+  for (int i = 0; i < kScanItems; ++i) sum += v[i];
+  int end;
+  int run = off + tile_exclusive(sum, !OFF && tiles > 1 ? state : nullptr, tile, s_wave, &end, [&](int i) {
+    int x = 0;  // a tile before this one is full
+    for (int q = __lane_id(); q < kTileItems; q += kWave) x += a.out_count[static_cast<int64_t>(i) * kTileItems + q];
+    return wave_sum(x);
+  });
+  if (tile == tiles - 1 && t == 0) {
+    *total = off + end;
+    if (off + end > a.links_cap) status_flag(status, PT_FLAG_LINKS_OVERFLOW);
   }
-  __syncthreads();
-  int run = tile_off[blockIdx.x] + s_wave[wave] + incl - sum;
-  int pos[kEmitItems];
+  int pos[kScanItems];
 #pragma unroll
-  for (int i = 0; i < kEmitItems; ++i) {
+  for (int i = 0; i < kScanItems; ++i) {
     pos[i] = run;
     run += v[i];
     s_pos[at + i] = pos[i];
   }
-  if (t == kEmitBlock - 1) s_pos[kScanTile] = run;  // the tile's end (cells past m count nothing)
-  if (vec) {
-    int4* p = reinterpret_cast<int4*>(out_start + first + at);
-#pragma unroll
-    for (int i = 0; i < kEmitItems / 4; ++i) p[i] = make_int4(pos[4 * i], pos[4 * i + 1], pos[4 * i + 2], pos[4 * i + 3]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < kEmitItems; ++i)
-      if (at + i < m) out_start[first + at + i] = pos[i];
-  }
+  if (t == kTileThreads - 1) s_pos[kTileItems] = run;  // the tile's end (cells past m count nothing)
+  store_items<VEC>(out_start, first + at, n, pos);
   __syncthreads();
   // the links of the cells with 1..kLocal, four rounds of cells at a time:
   // every record load of the rounds before any store
   const int4* sp = reinterpret_cast<const int4*>(a.spill);
   constexpr int kBatch = 4;
-  for (int r0 = 0; r0 < kEmitItems; r0 += kBatch) {
+  for (int r0 = 0; r0 < kScanItems; r0 += kBatch) {
     int cnt[kBatch], ps[kBatch];
     int4 q0[kBatch], q1[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const int c = (r0 + u) * kEmitBlock + t;
+      const int c = (r0 + u) * kTileThreads + t;
       ps[u] = c < m ? s_pos[c] : 0;
       cnt[u] = c < m ? s_pos[c + 1] - ps[u] : 0;
       q0[u] = q1[u] = make_int4(0, 0, 0, 0);
@@ -952,7 +930,7 @@ __global__ void __launch_bounds__(kEmitBlock) k_link_place(EmitArgs a, const int
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
       if (cnt[u] > 0 && cnt[u] <= kLocal)
-        emit_cell(a, static_cast<int>(first + (r0 + u) * kEmitBlock + t), cnt[u], ps[u], q0[u], q1[u]);
+        emit_cell(a, static_cast<int>(first + (r0 + u) * kTileThreads + t), cnt[u], ps[u], q0[u], q1[u]);
   }
 }
 
@@ -1017,24 +995,20 @@ __global__ void __launch_bounds__(kOvfWaves * kWave)
   }
 }
 
-__global__ void k_finish_links(const int32_t* count, int32_t cap, uint32_t* status) {
-  if (*count > cap) status_flag(status, PT_FLAG_LINKS_OVERFLOW);
-}
-
 }  // namespace
 
 // The index of the stored cells by outer hit alone (for the Fishbone), in
 // the workspace from its start; returns the bytes it takes.
 static size_t carve_outer_index(Carver& c, int n_hits, int cells_cap, OuterIndex* out, InCell** ent, int4** grp,
-                                int32_t** n_grp, int32_t** tmp) {
-  const int64_t scan_n = std::max<int64_t>(n_hits, cells_cap);
+                                int32_t** n_grp, int32_t** n_seg, uint64_t** state) {
   const int64_t chunks = std::max<int64_t>(1, (static_cast<int64_t>(cells_cap) + kIndexChunk - 1) / kIndexChunk);
   InCell* e = c.take<InCell>(cells_cap);
   int4* g = c.take<int4>(cells_cap);
   int32_t* ng = c.take<int32_t>(chunks);
+  int32_t* ns = c.take<int32_t>(static_cast<size_t>(n_hits));
   int32_t* sf = c.take<int32_t>(static_cast<size_t>(n_hits) + 1);
   int2* sg = c.take<int2>(cells_cap);
-  int32_t* t = c.take<int32_t>(scan_tmp_elems(scan_n));
+  uint64_t* t = c.take<uint64_t>(scan_state_words(n_hits));
   if (out) {
     out->ent = reinterpret_cast<const int2*>(e);
     out->seg = sg;
@@ -1042,14 +1016,15 @@ static size_t carve_outer_index(Carver& c, int n_hits, int cells_cap, OuterIndex
     *ent = e;
     *grp = g;
     *n_grp = ng;
-    *tmp = t;
+    *n_seg = ns;
+    *state = t;
   }
   return c.off;
 }
 
 size_t ws_outer_index(int n_hits, int cells_cap) {
   Carver c(nullptr);
-  return carve_outer_index(c, n_hits, cells_cap, nullptr, nullptr, nullptr, nullptr, nullptr);
+  return carve_outer_index(c, n_hits, cells_cap, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
 }
 
 pt_err build_outer_index(const pt_hits& h, const pt_cells& cells, Carver& c, OuterIndex& out, hipStream_t s) {
@@ -1057,35 +1032,43 @@ pt_err build_outer_index(const pt_hits& h, const pt_cells& cells, Carver& c, Out
   const int64_t chunks = std::max<int64_t>(1, (static_cast<int64_t>(cells.cap) + kIndexChunk - 1) / kIndexChunk);
   InCell* ent = nullptr;
   int4* grp = nullptr;
-  int32_t *n_grp = nullptr, *tmp = nullptr;
-  carve_outer_index(c, n, cells.cap, &out, &ent, &grp, &n_grp, &tmp);
+  int32_t *n_grp = nullptr, *n_seg = nullptr;
+  uint64_t* state = nullptr;
+  carve_outer_index(c, n, cells.cap, &out, &ent, &grp, &n_grp, &n_seg, &state);
   int32_t* seg_first = const_cast<int32_t*>(out.seg_first);
-  PT_HIP_CHECK(fill_i32(seg_first, 0, static_cast<int64_t>(n) + 1, s));
-  IndexArgs g{cells.count, cells.cap, cells.inner, cells.outer, h.layer, ent, grp, n_grp, seg_first, nullptr,
+  PT_HIP_CHECK(fill_i32(n_seg, 0, n, s));
+  PT_HIP_CHECK(fill_i32(reinterpret_cast<int32_t*>(state), 0, static_cast<int64_t>(2 * scan_state_words(n)), s));
+  IndexArgs g{cells.count, cells.cap, cells.inner, cells.outer, h.layer, ent, grp, n_grp, n_seg, nullptr,
               nullptr};
   k_cell_index<<<static_cast<unsigned>(chunks), kIndexBlock, 0, s>>>(g);
   PT_LAUNCH_CHECK();
-  PT_HIP_CHECK(exclusive_scan(seg_first, n, tmp, s));
+  PT_HIP_CHECK(exclusive_scan(n_seg, seg_first, n, nullptr, ScanTotal{}, state, s));
   k_seg_scatter<<<static_cast<unsigned>(chunks), kScatterBlock, 0, s>>>(cells.count, cells.cap, grp, n_grp, seg_first,
                                                                        const_cast<int2*>(out.seg));
   PT_LAUNCH_CHECK();
   return PT_OK;
 }
 
+// Scratch words cleared by k_hit_table: the states of the two scans and the
+// overflow count.
+static size_t link_words(int n_hits, int cells_cap) { return scan_state_words(n_hits) + scan_state_words(cells_cap) + 1; }
+static size_t off_tiles(int cells_cap) { return cells_cap > kLargeItems ? tiles_of(cells_cap, kTileItems) : 0; }
+
 size_t ws_links(int n_hits, int cells_cap) {
-  const int64_t scan_n = std::max<int64_t>(n_hits, cells_cap);
   const int64_t chunks = std::max<int64_t>(1, (static_cast<int64_t>(cells_cap) + kIndexChunk - 1) / kIndexChunk);
   Carver c(nullptr);
   c.take<double4>(n_hits);                  // hit table
   c.take<InCell>(cells_cap);                // index entries
   c.take<int4>(cells_cap);                  // groups of each block
   c.take<int32_t>(chunks);                  // groups per block
-  c.take<int32_t>(static_cast<size_t>(n_hits) + 1);     // segments per hit -> first segment
+  c.take<int32_t>(n_hits);                  // segments per hit
+  c.take<int32_t>(static_cast<size_t>(n_hits) + 1);     // first segment of each hit
   c.take<int2>(cells_cap);                  // segments
-  c.take<int32_t>(scan_tmp_elems(scan_n));
+  c.take<uint64_t>(link_words(n_hits, cells_cap));
   c.take<int32_t>(static_cast<size_t>(cells_cap) * kRow);  // records of the cells with links (two halves)
   c.take<int32_t>(cells_cap);               // overflow list
-  c.take<int32_t>(1);                       // overflow count
+  c.take<int32_t>(off_tiles(cells_cap));      // links of each tile of cells
+  c.take<int32_t>(off_tiles(cells_cap) + 1);  // ... and of those before it
   return c.off + 256;
 }
 
@@ -1099,36 +1082,39 @@ template <class T>
 static pt_err run_links(const pt_hits& h, const DevCfg& k, const pt_cells& cells, pt_links& L,
                         uint32_t* status, pt_workspace ws, hipStream_t s, int block) {
   const int n = h.n_hits;
-  const int64_t scan_n = std::max<int64_t>(n, cells.cap);
   const int64_t chunks = std::max<int64_t>(1, (static_cast<int64_t>(cells.cap) + kIndexChunk - 1) / kIndexChunk);
   Carver c(ws.ptr);
   double4* hx = c.take<double4>(n);
   InCell* ent = c.take<InCell>(cells.cap);
   int4* grp = c.take<int4>(cells.cap);
   int32_t* n_grp = c.take<int32_t>(chunks);
+  int32_t* n_seg = c.take<int32_t>(n);
   int32_t* seg_first = c.take<int32_t>(static_cast<size_t>(n) + 1);
   int2* seg = c.take<int2>(cells.cap);
-  int32_t* tmp = c.take<int32_t>(scan_tmp_elems(scan_n));
+  const size_t words = link_words(n, cells.cap);
+  uint64_t* scratch = c.take<uint64_t>(words);
   int32_t* spill = c.take<int32_t>(static_cast<size_t>(cells.cap) * kRow);
   int32_t* ovf = c.take<int32_t>(cells.cap);
-  int32_t* ovf_count = c.take<int32_t>(1);
+  const size_t n_off = off_tiles(cells.cap);
+  int32_t* tile_links = c.take<int32_t>(n_off);
+  int32_t* tile_off = c.take<int32_t>(n_off + 1);
+  uint64_t* seg_state = scratch;
+  uint64_t* place_state = seg_state + scan_state_words(n);
+  int32_t* ovf_count = reinterpret_cast<int32_t*>(place_state + scan_state_words(cells.cap));
   const T* x = static_cast<const T*>(h.x);
   const T* y = static_cast<const T*>(h.y);
   const T* z = static_cast<const T*>(h.z);
 
-  PT_HIP_CHECK(fill_i32(ovf_count, 0, 1, s));
-  PT_HIP_CHECK(fill_i32(seg_first, 0, static_cast<int64_t>(n) + 1, s));
-  if (n > 0) {
-    k_hit_table<T><<<grid_for(n, 256), 256, 0, s>>>(n, x, y, z, hx);
-    PT_LAUNCH_CHECK();
-  }
+  k_hit_table<T><<<grid_for(std::max<int64_t>(n, static_cast<int64_t>(words)), 256), 256, 0, s>>>(
+      n, x, y, z, hx, n_seg, scratch, static_cast<int>(words));
+  PT_LAUNCH_CHECK();
   void* tok = timing_begin(s);
-  IndexArgs g{cells.count, cells.cap, cells.inner, cells.outer, h.layer, ent, grp, n_grp, seg_first,
+  IndexArgs g{cells.count, cells.cap, cells.inner, cells.outer, h.layer, ent, grp, n_grp, n_seg,
               L.out_count, L.has_inner};
   k_cell_index<<<static_cast<unsigned>(chunks), kIndexBlock, 0, s>>>(g);
   timing_end(tok, "cell_index", s);
   PT_LAUNCH_CHECK();
-  PT_HIP_CHECK(exclusive_scan(seg_first, n, tmp, s));
+  PT_HIP_CHECK(exclusive_scan(n_seg, seg_first, n, nullptr, ScanTotal{}, seg_state, s));
   tok = timing_begin(s);
   k_seg_scatter<<<static_cast<unsigned>(chunks), kScatterBlock, 0, s>>>(cells.count, cells.cap, grp, n_grp, seg_first, seg);
   timing_end(tok, "link_segments", s);
@@ -1147,22 +1133,27 @@ static pt_err run_links(const pt_hits& h, const DevCfg& k, const pt_cells& cells
     PT_LAUNCH_CHECK();
   }
   timing_end(tok, "links", s);
-  // first link of each cell and the links: the tile sums of the counts are
-  // scanned, then each tile scans itself and places its links
-  const int32_t* tile_off = nullptr;
-  PT_HIP_CHECK(scan_tile_offsets(L.out_count, cells.cap, cells.count, tmp, s, &tile_off));
+  if (n_off) {
+    PT_HIP_CHECK(tile_sums(L.out_count, cells.cap, cells.count, tile_links, s));
+    PT_HIP_CHECK(exclusive_scan(tile_links, tile_off, static_cast<int64_t>(n_off), nullptr, ScanTotal{}, place_state, s));
+  }
   tok = timing_begin(s);
   EmitArgs e{cells.count, cells.cap, L.out_start, L.out_count, spill, L.cap, L.in_cell, L.out_cell};
   {
-    const int64_t tiles = std::max<int64_t>(1, (static_cast<int64_t>(cells.cap) + kScanTile - 1) / kScanTile);
-    k_link_place<<<static_cast<unsigned>(tiles), kEmitBlock, 0, s>>>(e, tile_off, L.out_start, L.count);
+    const unsigned tiles = static_cast<unsigned>(tiles_of(cells.cap, kTileItems));
+    const bool vec = aligned16(L.out_count) && aligned16(L.out_start);
+    auto place = [&](auto kernel) {
+      kernel<<<tiles, kTileThreads, 0, s>>>(e, place_state, tile_off, L.out_start, L.count, status);
+    };
+    if (n_off)
+      vec ? place(k_link_place<true, true>) : place(k_link_place<false, true>);
+    else
+      vec ? place(k_link_place<true, false>) : place(k_link_place<false, false>);
   }
   timing_end(tok, "link_emit", s);
   PT_LAUNCH_CHECK();
   k_links_overflow<T><<<1024, kOvfWaves * kWave, 0, s>>>(k, a, cells.inner, h.layer, L.out_start, L.cap, L.in_cell,
                                                          L.out_cell);
-  PT_LAUNCH_CHECK();
-  k_finish_links<<<1, 1, 0, s>>>(L.count, L.cap, status);
   PT_LAUNCH_CHECK();
   return PT_OK;
 }

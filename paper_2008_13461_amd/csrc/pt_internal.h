@@ -79,12 +79,18 @@ struct Carver {
 };
 
 // Workspace needed by each call (bytes); the public size is their maximum.
-size_t ws_doublets(int n_hits, int n_events, int n_bins);
+size_t ws_doublets(int n_hits, int n_events, int n_bins, int raw_cells);  // raw_cells: capacity when the Fishbone is on, else 0
 size_t ws_links(int n_hits, int cells_cap);
 size_t ws_ntuplets(int cells_cap, int tuplets_cap);
 size_t ws_fit(int n_max, int n_modules);
 size_t ws_ambiguity(int n_hits, int cells_cap, int n_max);
+// The Fishbone filters the cells as the doublet step finds them, in the
+// workspace, into the output: carve_raw_cells carves them (the rest of
+// `cells` is shared), launch_fishbone takes its scratch behind them.
 size_t ws_fishbone(int n_hits, int cells_cap);
+pt_cells carve_raw_cells(Carver& c, const pt_cells& cells, int cells_cap);
+pt_err launch_fishbone(const pt_hits& h, const DevCfg& k, const pt_cells& raw, pt_cells& cells, Carver c,
+                       hipStream_t s);
 // Host-side set-up of the Fishbone's launch shapes (device queries), done
 // before a plan captures its graph.
 void fishbone_prepare();
@@ -102,25 +108,36 @@ size_t ws_outer_index(int n_hits, int cells_cap);
 pt_err build_outer_index(const pt_hits& h, const pt_cells& cells, Carver& c, OuterIndex& out, hipStream_t s);
 size_t ws_vertices(int n_events, int n_max);
 
-// Device-wide exclusive scan of n int32 values in place; data[n] receives the
-// total.  tmp must hold scan_tmp_elems(n) int32.
-size_t scan_tmp_elems(int64_t n);
-hipError_t exclusive_scan(int32_t* data, int64_t n, int32_t* tmp, hipStream_t s);
-// The same over the first min(*n_dev, n) values, n_dev a device count; the
-// total goes to data[min(*n_dev, n)].
-hipError_t exclusive_scan_dev(int32_t* data, int64_t n, const int32_t* n_dev, int32_t* tmp, hipStream_t s);
-// Out of place: dst[i] = src[0] + .. + src[i-1] over the first
-// min(*n_dev, n) values (all n when n_dev is null), the total to *total
-// (dst[that count] when total is null).  src may equal dst.
-hipError_t exclusive_scan_to(const int32_t* src, int32_t* dst, int64_t n, const int32_t* n_dev, int32_t* total,
-                             int32_t* tmp, hipStream_t s);
-// The first step of such a scan alone, for a kernel that scans its own tile
-// of kScanTile values: *offsets (in tmp) receives, for each of the
-// ceil(n / kScanTile) tiles, the sum of the values before it, and after them
-// the total (the values counted as above).
-constexpr int kScanTile = 4096;
-hipError_t scan_tile_offsets(const int32_t* src, int64_t n, const int32_t* n_dev, int32_t* tmp, hipStream_t s,
-                             const int32_t** offsets);
+// Device-wide exclusive scans, one kernel each: every work-group scans a tile
+// of kTileItems consecutive values, kScanItems per thread, and takes the sum of
+// the tiles before its own from their states (see tile_before below).  state
+// holds scan_state_words(n) words, zero before the kernel runs; a scan of one
+// tile does not use it.
+constexpr int kTileThreads = 256;
+constexpr int kScanItems = 16;
+constexpr int kTileItems = kTileThreads * kScanItems;
+constexpr size_t tiles_of(int64_t n, int64_t tile) { return n > 0 ? static_cast<size_t>((n + tile - 1) / tile) : 1; }
+constexpr size_t scan_state_words(int64_t n) { return tiles_of(n, kTileItems); }
+// Above this many cells a listing takes its tiles' offsets from a pass over
+// their sums instead: the chain of states (8 ns a tile) is then longer than
+// the pass (64 PU200 events, 47 000 tiles: k_link_place 1.28 ms in one kernel,
+// 0.75 after 0.16; one PU200 event, 730 tiles: 25 us in one, 30 with the pass).
+constexpr int64_t kLargeItems = int64_t(1) << 24;
+// dst[i] = src[0] + .. + src[i-1] over the first m = min(*n_dev, n) values,
+// n_dev a device count (n when null), dst[m] the total, which also goes to
+// *total when given, with `flag` set in the status when it exceeds cap.  src
+// and dst must not overlap.
+struct ScanTotal {
+  int32_t* total = nullptr;
+  int32_t cap = 0x7fffffff;
+  uint32_t flag = 0;
+  uint32_t* status = nullptr;
+};
+hipError_t exclusive_scan(const int32_t* src, int32_t* dst, int64_t n, const int32_t* n_dev, const ScanTotal& t,
+                          uint64_t* state, hipStream_t s);
+// Sums of the tiles of kTileItems of the first min(*n_dev, n) values (0 past
+// them), one per tile of n.
+hipError_t tile_sums(const int32_t* src, int64_t n, const int32_t* n_dev, int32_t* sums, hipStream_t s);
 
 // Fill helpers (graph-safe: kernels, not hipMemsetAsync).
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
@@ -218,6 +235,174 @@ __device__ __forceinline__ float wave_min(float v) {
   });
   return __int_as_float(__builtin_amdgcn_readlane(r, kWave - 1));
 }
+
+// ---------------------------------------------------------------------------
+// Prefixes over the tiles of one kernel, tile i the work-group i.  The state of
+// a tile is a value in the low word, and above it 0 (not there yet), kTileSum
+// (the tile's own sum) or kTilePrefix (the sum up to and including it).  Value
+// and flag are one atomic, so no other memory is ordered by it.  A work-group
+// waits for the tiles before its own a bounded number of polls and then sums
+// the missing tile itself, from the input (which no tile overwrites): every
+// wait ends, in whatever order the work-groups are started.  (A ticket per
+// tile, taken in the order the work-groups start, orders them too, but one
+// counter hands out a ticket every 11 ns: 15 us for the tiles of one pileup-200
+// event.)
+constexpr uint64_t kTileSum = uint64_t(1) << 32, kTilePrefix = uint64_t(2) << 32;
+constexpr int kPolls = 256;
+
+// The sum of the tiles before `tile`, whose own sum is given; called by one
+// wavefront.  sum_of(i), called by the whole wavefront, is the sum of tile i.
+// Lanes look back 64 tiles at a time to the last one whose prefix is known, the
+// loads of kLookBack such steps in flight together: a state comes from beyond
+// the XCD's own L2, and the tiles of every resident work-group lie between a
+// tile and the last known prefix.
+constexpr int kLookBack = 8;
+template <class F>
+__device__ inline int32_t tile_before(uint64_t* state, int tile, int32_t sum, F sum_of) {
+  const int lane = __lane_id();
+  auto load = [&](int i) {
+    return i >= 0 ? __hip_atomic_load(state + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kTilePrefix;
+  };
+  if (lane == 0)
+    __hip_atomic_store(state + tile, (tile == 0 ? kTilePrefix : kTileSum) | static_cast<uint32_t>(sum),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int32_t before = 0;
+  bool done = tile == 0;
+  for (int at = tile - 1; !done; at -= kLookBack * kWave) {
+    uint64_t v[kLookBack];
+#pragma unroll
+    for (int k = 0; k < kLookBack; ++k) v[k] = load(at - k * kWave - lane);
+#pragma unroll
+    for (int k = 0; k < kLookBack; ++k) {
+      if (done) continue;
+      const int first = at - k * kWave;  // lane 0's tile
+      uint64_t known;                    // lanes whose tile's prefix is known
+      for (int polls = 0;; ++polls) {
+        known = __ballot(v[k] >= kTilePrefix);
+        const uint64_t wanted = known ? (known & (~known + 1)) * 2 - 1 : ~uint64_t(0);  // up to the nearest
+        const uint64_t missing = __ballot(v[k] == 0) & wanted;
+        if (!missing) break;
+        if (polls < kPolls) {
+          if (v[k] == 0) v[k] = load(first - lane);
+        } else {
+          const int l = __builtin_ctzll(missing);
+          const int32_t x = sum_of(first - l);
+          if (lane == l) v[k] = kTileSum | static_cast<uint32_t>(x);
+        }
+      }
+      const int stop = known ? __builtin_ctzll(known) : kWave;
+      before += wave_sum(lane <= stop ? static_cast<int32_t>(static_cast<uint32_t>(v[k])) : 0);
+      done = known != 0;
+    }
+  }
+  if (lane == 0 && tile > 0)
+    __hip_atomic_store(state + tile, kTilePrefix | static_cast<uint32_t>(before + sum), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  return before;
+}
+
+// Exclusive prefix of v over the work-group (kTileThreads) and, with a state,
+// the tiles before its own; *end receives the sum up to and including the
+// tile, s_wave[0] the sum before it.  s_wave holds kTileThreads / kWave + 1 words.
+template <class F>
+__device__ inline int32_t tile_exclusive(int32_t v, uint64_t* state, int tile, int32_t* s_wave, int32_t* end, F sum_of) {
+  constexpr int kWaves = kTileThreads / kWave;
+  const int lane = __lane_id(), wave = static_cast<int>(threadIdx.x) / kWave;
+  const int32_t incl = wave_incl_scan(v);
+  if (lane == kWave - 1) s_wave[wave] = incl;
+  __syncthreads();
+  if (wave == 0) {
+    const int32_t w = lane < kWaves ? s_wave[lane] : 0;
+    const int32_t wi = wave_incl_scan(w);
+    const int32_t sum = __builtin_amdgcn_readlane(wi, kWaves - 1);
+    const int32_t before = state ? tile_before(state, tile, sum, sum_of) : 0;
+    if (lane < kWaves) s_wave[lane] = before + wi - w;
+    if (lane == 0) s_wave[kWaves] = before + sum;
+  }
+  __syncthreads();
+  *end = s_wave[kWaves];
+  return s_wave[wave] + incl - v;
+}
+__device__ inline int32_t block_exclusive(int32_t v, int32_t* s_wave, int32_t* total) {
+  return tile_exclusive(v, nullptr, 0, s_wave, total, [](int) { return 0; });
+}
+
+// Positions of a tile of four runs of flags, c[i] the number of set flags of
+// this thread's group in run i (the groups of a run in thread order): pos[i]
+// is the number of set flags before c[i]'s first, in the tile and (with a
+// state) those before it, *end the number up to the tile's end.  s_wave holds
+// 2 kTileThreads / kWave + 3 words.  The sum of a run fits 15 bits.
+template <class F>
+__device__ inline void tile_positions(const int (&c)[4], uint64_t* state, int tile, int32_t* s_wave, int (&pos)[4],
+                                      int32_t* end, F sum_of) {
+  constexpr int kWaves = kTileThreads / kWave;
+  const int lane = __lane_id(), wave = static_cast<int>(threadIdx.x) / kWave;
+  const int a = c[0] | c[1] << 16, b = c[2] | c[3] << 16;
+  const int ia = wave_incl_scan(a), ib = wave_incl_scan(b);
+  if (lane == kWave - 1) {
+    s_wave[wave] = ia;
+    s_wave[kWaves + wave] = ib;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int wa = lane < kWaves ? s_wave[lane] : 0, wb = lane < kWaves ? s_wave[kWaves + lane] : 0;
+    const int sa = wave_incl_scan(wa), sb = wave_incl_scan(wb);
+    const int ta = __builtin_amdgcn_readlane(sa, kWaves - 1), tb = __builtin_amdgcn_readlane(sb, kWaves - 1);
+    const int sum = (ta & 0xFFFF) + (ta >> 16) + (tb & 0xFFFF) + (tb >> 16);
+    const int32_t before = state ? tile_before(state, tile, sum, sum_of) : 0;
+    if (lane < kWaves) {  // the wavefronts' first positions within each run
+      s_wave[lane] = sa - wa;
+      s_wave[kWaves + lane] = sb - wb;
+    }
+    if (lane == 0) {
+      s_wave[2 * kWaves] = before;
+      s_wave[2 * kWaves + 1] = ta;
+      s_wave[2 * kWaves + 2] = tb;
+    }
+  }
+  __syncthreads();
+  const int ta = s_wave[2 * kWaves + 1], tb = s_wave[2 * kWaves + 2];
+  const int ea = s_wave[wave] + ia - a, eb = s_wave[kWaves + wave] + ib - b;
+  const int b0 = s_wave[2 * kWaves], b1 = b0 + (ta & 0xFFFF), b2 = b1 + (ta >> 16), b3 = b2 + (tb & 0xFFFF);
+  pos[0] = b0 + (ea & 0xFFFF);
+  pos[1] = b1 + (ea >> 16);
+  pos[2] = b2 + (eb & 0xFFFF);
+  pos[3] = b3 + (eb >> 16);
+  *end = b3 + (tb >> 16);
+}
+
+// kScanItems consecutive values of a thread, from index `base` of n (16-byte
+// vectors where they lie below n, when VEC); values past n are 0.
+template <bool VEC>
+__device__ inline void load_items(const int32_t* src, int64_t base, int64_t n, int32_t (&v)[kScanItems]) {
+#pragma unroll
+  for (int i = 0; i < kScanItems; i += 4) {
+    if (VEC && base + i + 4 <= n) {
+      const int4 q = *reinterpret_cast<const int4*>(src + base + i);
+      v[i] = q.x;
+      v[i + 1] = q.y;
+      v[i + 2] = q.z;
+      v[i + 3] = q.w;
+    } else {
+#pragma unroll
+      for (int k = i; k < i + 4; ++k) v[k] = base + k < n ? src[base + k] : 0;
+    }
+  }
+}
+template <bool VEC>
+__device__ inline void store_items(int32_t* dst, int64_t base, int64_t n, const int32_t (&v)[kScanItems]) {
+#pragma unroll
+  for (int i = 0; i < kScanItems; i += 4) {
+    if (VEC && base + i + 4 <= n) {
+      *reinterpret_cast<int4*>(dst + base + i) = make_int4(v[i], v[i + 1], v[i + 2], v[i + 3]);
+    } else {
+#pragma unroll
+      for (int k = i; k < i + 4; ++k)
+        if (base + k < n) dst[base + k] = v[k];
+    }
+  }
+}
+__host__ __device__ inline bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
 // Number of set bits of a wave mask below this lane.
 __device__ inline int lane_prefix(uint64_t mask) {

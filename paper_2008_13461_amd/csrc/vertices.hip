@@ -63,7 +63,8 @@ struct VtxArgs {
   // scratch, [n_max] unless noted
   uint8_t* use;
   int32_t* ev_of;        // event of each track, -1 when it takes no part
-  int32_t* ev_count;     // [n_events + 1], scanned in place into the starts
+  int32_t* ev_n;         // [n_events] tracks of each event
+  int32_t* ev_count;     // [n_events + 1] first list entry of each event (the scan of ev_n)
   int32_t* ev_cursor;    // [n_events]
   int32_t* list;         // tracks grouped by event
   uint64_t* skey;        // [2 n_max] sort keys (padded per event)
@@ -93,7 +94,9 @@ struct VtxArgs {
   int32_t* rec1;         // per root position: record slots of the two parts of a split tree, -1
   int32_t* rec2;
   int32_t* vlocal;       // per position: rank of the track's vertex in its event, -1
-  int32_t* ev_nvtx;      // [n_events + 1] records per event, scanned into the first vertex of each event
+  int32_t* ev_nvtx;      // [n_events] records per event (their scan: event_first)
+  uint64_t* state;       // of the two scans over the events
+  int32_t state_words;   // of each
   // outputs
   double *oz, *ovar, *ochi2, *osum;
   int32_t *ondf, *on;
@@ -146,11 +149,12 @@ __global__ void k_vtx_clear(VtxArgs a) {
     a.use[i] = a.selected ? 0 : 1;
     a.track_vertex[i] = -1;
   }
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e <= a.n_events; e += gridDim.x * blockDim.x) {
-    a.ev_count[e] = 0;
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < a.n_events; e += gridDim.x * blockDim.x) {
+    a.ev_n[e] = 0;
     a.ev_nvtx[e] = 0;
-    if (e < a.n_events) a.ev_cursor[e] = 0;
+    a.ev_cursor[e] = 0;
   }
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < 2 * a.state_words; i += gridDim.x * blockDim.x) a.state[i] = 0;
 }
 
 __global__ void k_vtx_mark(VtxArgs a) {
@@ -184,7 +188,7 @@ __global__ void k_vtx_events(VtxArgs a) {
       if (a.n_events > 0 && a.event_offsets[lo] <= h0 && h0 < a.event_offsets[lo + 1]) e = lo;
     }
     a.ev_of[i] = e;
-    wave_add(a.ev_count, e);
+    wave_add(a.ev_n, e);
   }
 }
 
@@ -594,14 +598,6 @@ __global__ void k_vtx_write(VtxArgs a) {
   if (over) status_flag(a.status, PT_FLAG_VERTICES_OVERFLOW);
 }
 
-// event_first from the scanned vertex counts, and the total.
-__global__ void k_vtx_event_first(VtxArgs a) {
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e <= a.n_events; e += gridDim.x * blockDim.x) {
-    a.event_first[e] = a.ev_nvtx[e];
-    if (e == a.n_events) *a.n_vertices = a.ev_nvtx[e];
-  }
-}
-
 }  // namespace
 
 size_t ws_vertices(int n_events, int n_max) {
@@ -609,6 +605,7 @@ size_t ws_vertices(int n_events, int n_max) {
   const size_t n = static_cast<size_t>(n_max) + 1, E = static_cast<size_t>(n_events) + 1;
   c.take<uint8_t>(n);        // use
   c.take<int32_t>(n);        // ev_of
+  c.take<int32_t>(E);        // ev_n
   c.take<int32_t>(E);        // ev_count
   c.take<int32_t>(E);        // ev_cursor
   c.take<int32_t>(n);        // list
@@ -623,7 +620,7 @@ size_t ws_vertices(int n_events, int n_max) {
   for (int q = 0; q < 5; ++q) c.take<int32_t>(n);  // rndf rn rfirst rslot vlocal
   for (int q = 0; q < 5; ++q) c.take<int32_t>(n);  // pev rrank rec0 rec1 rec2
   c.take<int32_t>(E);        // ev_nvtx
-  c.take<int32_t>(scan_tmp_elems(static_cast<int64_t>(E)));
+  c.take<uint64_t>(2 * scan_state_words(n_events));
   return c.off + 256;
 }
 
@@ -658,6 +655,7 @@ pt_err launch_vertices(const pt_hits& h, const DevCfg& k, const pt_ntuplets& T, 
   a.K = k.K;
   a.use = c.take<uint8_t>(n);
   a.ev_of = c.take<int32_t>(n);
+  a.ev_n = c.take<int32_t>(E);
   a.ev_count = c.take<int32_t>(E);
   a.ev_cursor = c.take<int32_t>(E);
   a.list = c.take<int32_t>(n);
@@ -688,7 +686,8 @@ pt_err launch_vertices(const pt_hits& h, const DevCfg& k, const pt_ntuplets& T, 
   a.rec1 = c.take<int32_t>(n);
   a.rec2 = c.take<int32_t>(n);
   a.ev_nvtx = c.take<int32_t>(E);
-  int32_t* tmp = c.take<int32_t>(scan_tmp_elems(static_cast<int64_t>(E)));
+  a.state_words = static_cast<int32_t>(scan_state_words(h.n_events));
+  a.state = c.take<uint64_t>(2 * static_cast<size_t>(a.state_words));
   a.oz = out.z;
   a.ovar = out.var;
   a.ochi2 = out.chi2;
@@ -705,7 +704,7 @@ pt_err launch_vertices(const pt_hits& h, const DevCfg& k, const pt_ntuplets& T, 
   if (selected) k_vtx_mark<<<g, 256, 0, s>>>(a);
   k_vtx_events<<<g, 256, 0, s>>>(a);
   PT_LAUNCH_CHECK();
-  PT_HIP_CHECK(exclusive_scan(a.ev_count, h.n_events, tmp, s));
+  PT_HIP_CHECK(exclusive_scan(a.ev_n, a.ev_count, h.n_events, nullptr, ScanTotal{}, a.state, s));
   k_vtx_scatter<<<g, 256, 0, s>>>(a);
   PT_LAUNCH_CHECK();
   const int gp = grid_for(n_max, 256, 16384);   // flat over the sorted positions
@@ -724,8 +723,8 @@ pt_err launch_vertices(const pt_hits& h, const DevCfg& k, const pt_ntuplets& T, 
   }
   k_vtx_members<<<gp, 256, 0, s>>>(a);
   PT_LAUNCH_CHECK();
-  PT_HIP_CHECK(exclusive_scan(a.ev_nvtx, h.n_events, tmp, s));
-  k_vtx_event_first<<<grid_for(h.n_events + 1, 256), 256, 0, s>>>(a);
+  PT_HIP_CHECK(exclusive_scan(a.ev_nvtx, a.event_first, h.n_events, nullptr, ScanTotal{a.n_vertices},
+                              a.state + a.state_words, s));
   k_vtx_write<<<gp, 256, 0, s>>>(a);
   PT_LAUNCH_CHECK();
   return PT_OK;
