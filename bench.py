@@ -42,7 +42,7 @@ KERNEL_SYMBOL = {"doublets_count": "k_doublets<false>", "doublets_write": "k_dou
                  "cell_index": "k_cell_index", "link_segments": "k_seg_scatter", "links": "k_link_hits",
                  "link_emit": "k_link_place", "root_count": "k_root_count", "root_write": "k_mask_write",
                  "dfs_count": "k_dfs<true>", "dfs_write": "k_dfs<false>", "fit_fwd": "k_fit<4,6>",
-                 "fit_bwd": "k_grad<4,6>"}
+                 "fit_bwd": "k_grad"}
 # Algorithmic work per unit, for the roofline of whichever kernel dominates:
 #  links: 12 B per candidate pair the search examines (the two segments'
 #    dr, dz as the test needs them, less what the wavefront shares) and 8 B

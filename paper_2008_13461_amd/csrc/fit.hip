@@ -1,13 +1,16 @@
 // Broken-line fit and its adjoint on the GPU (paper section 3.4: one thread
 // per n-tuplet).
 //
-// Tracks are first binned by their number of hits, so that each
-// instantiation fit<N> runs over a dense list with its own register budget
-// (every per-hit quantity of a track lives in registers).  In the
-// single-precision mode with the double fallback, tracks whose transverse
-// system is too stiff for float (high momentum: the scattering kinks weigh
-// far more than the measurements) are put on a list and refitted entirely in
-// double by a second kernel.
+// Tracks are first binned by their number of hits, so that a wavefront takes
+// 64 tracks of one number N and runs the instantiation fit<N> alone (every
+// per-hit quantity of a track lives in registers).  Up to kMergedTracks one
+// kernel holds all of them: a fit is a long serial chain (20 us for four hits,
+// 40 for eight), and a kernel for each range of N pays the chains of all one
+// after the other.  Beyond, a kernel per range has its own register budget.
+// In the single-precision mode with the double fallback, tracks whose
+// transverse system is too stiff for float (high momentum: the scattering
+// kinks weigh far more than the measurements) are put on a list per N and
+// refitted entirely in double by a second kernel.
 //
 // The adjoint recomputes the forward fit in registers and sweeps it back
 // (fit_core.h).  Hit gradients are added with float atomics (hits can be
@@ -31,6 +34,16 @@ constexpr int kNBins = kMaxHits - kMinN + 1;  // N = 3..8
 constexpr int kBlock = 256;
 constexpr int kBwdBlocks = 256;
 constexpr int kRefitBlock = 64;
+// Counters: the bins', and on a cache line of their own the refit lists', whose
+// atomics would hold up every read of the bins'.
+constexpr int kRedoCounters = 64;
+constexpr int kCounters = kRedoCounters + kNBins;
+// Tracks up to which one kernel fits them whatever their number of hits (see
+// above): its registers leave one wavefront per SIMD, which costs 1.5 times the
+// time on dense lists with covariances (9.2 million triplets: 1.78 ms against 1.22)
+// and 1.07 on a million tracks without (204 us against 190), while 77 777 tracks
+// with covariances take 43 us instead of 113 and 1500 take 25 instead of 40.
+constexpr int kMergedTracks = 131072;
 
 struct FitArgs {
   int32_t dtype;
@@ -50,8 +63,8 @@ struct FitArgs {
   // binning
   int32_t* bins;             // [kNBins][n_max]
   int32_t* bin_count;        // [kNBins]
-  int32_t* redo;             // [n_max] tracks refitted in double
-  int32_t* redo_count;
+  int32_t* redo;             // [n_max] tracks refitted in double, a bin's behind those of the bins before
+  int32_t* redo_count;       // [kNBins]
   // forward outputs
   void* params;
   void* chi2;
@@ -95,6 +108,23 @@ __device__ inline int track_bin(const FitArgs& a, int i, int n) {
   return nh >= kMinN && nh <= kMaxHits ? nh - kMinN : -1;
 }
 
+// Tracks with an invalid hit count get a failed status (OT the type of the
+// outputs; void in the adjoint, which has none).
+template <class OT>
+__device__ inline void reject(const FitArgs& a, int i) {
+  if constexpr (!std::is_void<OT>::value) {
+    OT* P = static_cast<OT*>(a.params) + static_cast<int64_t>(i) * 5;
+    for (int q = 0; q < 5; ++q) P[q] = OT(NAN);
+    static_cast<OT*>(a.chi2)[i] = OT(NAN);
+    if (a.cov)
+      for (int q = 0; q < 15; ++q) static_cast<OT*>(a.cov)[static_cast<int64_t>(i) * 15 + q] = OT(NAN);
+    a.track_status[i] = fit::ST_FAILED;
+    status_add(a.status, PT_ST_FIT_FAILED, 1);
+    status_flag(a.status, PT_FLAG_FIT_FAILED);
+  }
+}
+
+template <class OT>
 __global__ void __launch_bounds__(kBlock) k_bin(FitArgs a) {
   constexpr int kWaves = kBlock / kWave;
   __shared__ int32_t s_cnt[kWaves][kNBins];
@@ -110,7 +140,9 @@ __global__ void __launch_bounds__(kBlock) k_bin(FitArgs a) {
 #pragma unroll
   for (int b = 0; b < kNBins; ++b) cnt[b] = 0;
   for (int i0 = lo; i0 < hi; i0 += kBlock) {
-    const int bin = track_bin(a, i0 + threadIdx.x, hi);
+    const int i = i0 + threadIdx.x;
+    const int bin = track_bin(a, i, hi);
+    if (i < hi && bin < 0) reject<OT>(a, i);
 #pragma unroll
     for (int b = 0; b < kNBins; ++b) cnt[b] += __popcll(__ballot(bin == b));
   }
@@ -148,29 +180,6 @@ __global__ void __launch_bounds__(kBlock) k_bin(FitArgs a) {
       s_run[threadIdx.x] += c;
     }
     __syncthreads();
-  }
-}
-
-// Tracks with an invalid hit count get a failed status.
-template <class OT>
-__global__ void k_reject(FitArgs a) {
-  const int n = n_tracks(a);
-  uint32_t bad = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const int nh = a.tup_n[track_row(a, i)];
-    if (nh < kMinN || nh > kMaxHits) {
-      OT* P = static_cast<OT*>(a.params) + static_cast<int64_t>(i) * 5;
-      for (int q = 0; q < 5; ++q) P[q] = OT(NAN);
-      static_cast<OT*>(a.chi2)[i] = OT(NAN);
-      if (a.cov)
-        for (int q = 0; q < 15; ++q) static_cast<OT*>(a.cov)[static_cast<int64_t>(i) * 15 + q] = OT(NAN);
-      a.track_status[i] = fit::ST_FAILED;
-      ++bad;
-    }
-  }
-  if (bad) {
-    status_add(a.status, PT_ST_FIT_FAILED, bad);
-    status_flag(a.status, PT_FLAG_FIT_FAILED);
   }
 }
 
@@ -223,8 +232,18 @@ __device__ inline bool load_track(const FitArgs& a, const uint8_t* layer_barrel,
   return ok;
 }
 
-// Forward fit of the tracks in bin N (LIST = false) or on the double-refit
-// list (LIST = true, any N, dispatched at run time).
+// First place of bin N in the double-refit list.
+__device__ inline int redo_first(const FitArgs& a, int N) {
+  int at = 0;
+  for (int b = 0; b < N - kMinN; ++b) at += a.bin_count[b];
+  return at;
+}
+template <int N>
+__device__ inline void list_redo(const FitArgs& a, int i) {
+  a.redo[redo_first(a, N) + atomicAdd(a.redo_count + (N - kMinN), 1)] = i;
+}
+
+// Forward fit of one track.
 template <int N, class S, class HT, class OT, bool COV>
 __device__ inline void fit_one(const DevCfg& k, const fit::Consts& C, const FitArgs& a, int i, bool fallback,
                                uint32_t& n_bad, uint32_t& n_fail, uint32_t& n_redo) {
@@ -237,8 +256,7 @@ __device__ inline void fit_one(const DevCfg& k, const fit::Consts& C, const FitA
   // Stiff systems, and systems whose single-precision solve broke down, are
   // solved again in double.
   if (fallback && ok && (st == fit::ST_FAILED || (st == fit::ST_OK && double(f.cond) > C.thr))) {
-    const int slot = atomicAdd(a.redo_count, 1);
-    a.redo[slot] = i;
+    list_redo<N>(a, i);
     ++n_redo;
     return;  // written by the double-precision refit
   }
@@ -279,40 +297,49 @@ __device__ inline void flush_counts(const FitArgs& a, uint32_t n_bad, uint32_t n
   if (n_redo) status_add(a.status, PT_ST_FIT_F64, n_redo);
 }
 
-// Work item j of the bins NLO..NHI (in bin order) -> (N, track index).
-template <int NLO, int NHI>
-__device__ inline int bin_item(const FitArgs& a, int j, int& nh) {
-  int base = 0;
+// The lists of tracks with NLO..NHI hits are dealt out 64 tracks of one list
+// per wavefront, the longest fits first.  Wavefronts that this takes:
+template <int NLO = kMinN, int NHI = kMaxHits>
+__device__ inline int list_waves(const int32_t* count) {
+  int w = 0;
 #pragma unroll
-  for (int N = NLO; N <= NHI; ++N) {
-    const int c = a.bin_count[N - kMinN];
-    if (j < base + c) {
-      nh = N;
-      return a.bins[static_cast<int64_t>(N - kMinN) * a.n_max + (j - base)];
+  for (int b = NLO - kMinN; b <= NHI - kMinN; ++b) w += (count[b] + kWave - 1) / kWave;
+  return w;
+}
+// Portion w of them: its number of hits, and this lane's place in that list
+// (-1 past its end).  Uniform but for the place.
+template <int NLO = kMinN, int NHI = kMaxHits>
+__device__ inline int list_place(const int32_t* count, int w, int& place) {
+  place = -1;
+  for (int b = NHI - kMinN; b >= NLO - kMinN; --b) {
+    const int c = count[b], waves = (c + kWave - 1) / kWave;
+    if (w < waves) {
+      const int at = w * kWave + __lane_id();
+      if (at < c) place = at;
+      return __builtin_amdgcn_readfirstlane(b + kMinN);
     }
-    base += c;
+    w -= waves;
   }
-  nh = 0;
-  return -1;
+  return 0;
 }
-
-template <int NLO, int NHI>
-__device__ inline int bin_total(const FitArgs& a) {
-  int t = 0;
-#pragma unroll
-  for (int N = NLO; N <= NHI; ++N) t += a.bin_count[N - kMinN];
-  return t;
+// This wavefront's index and the number of wavefronts of the launch.
+// Neighbouring wavefronts take neighbouring portions.
+__device__ inline int wave_index() {
+  return __builtin_amdgcn_readfirstlane(static_cast<int>((blockIdx.x * blockDim.x + threadIdx.x) / kWave));
 }
+__device__ inline int wave_total() { return static_cast<int>(gridDim.x * blockDim.x / kWave); }
 
 // Forward fit of the tracks with NLO..NHI hits.
 template <int NLO, int NHI, class S, class HT, class OT, bool COV>
 __global__ void __launch_bounds__(kBlock) k_fit(DevCfg k, FitArgs a, bool fallback) {
   const fit::Consts C = consts_of(k);
-  const int m = bin_total<NLO, NHI>(a);
+  const int waves = list_waves<NLO, NHI>(a.bin_count), step = wave_total();
   uint32_t n_bad = 0, n_fail = 0, n_redo = 0;
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < m; j += gridDim.x * blockDim.x) {
-    int nh;
-    const int i = bin_item<NLO, NHI>(a, j, nh);
+  for (int w = wave_index(); w < waves; w += step) {
+    int p;
+    const int nh = list_place<NLO, NHI>(a.bin_count, w, p);
+    if (p < 0) continue;
+    const int i = a.bins[static_cast<int64_t>(nh - kMinN) * a.n_max + p];
     if (NLO <= 3 && 3 <= NHI && nh == 3) fit_one<3, S, HT, OT, COV>(k, C, a, i, fallback, n_bad, n_fail, n_redo);
     if (NLO <= 4 && 4 <= NHI && nh == 4) fit_one<4, S, HT, OT, COV>(k, C, a, i, fallback, n_bad, n_fail, n_redo);
     if (NLO <= 5 && 5 <= NHI && nh == 5) fit_one<5, S, HT, OT, COV>(k, C, a, i, fallback, n_bad, n_fail, n_redo);
@@ -324,40 +351,23 @@ __global__ void __launch_bounds__(kBlock) k_fit(DevCfg k, FitArgs a, bool fallba
 }
 
 // Double-precision refit of the listed tracks; outputs in OT.
-template <class HT, class OT>
+template <class HT, class OT, bool COV>
 __global__ void __launch_bounds__(kRefitBlock) k_refit(DevCfg k, FitArgs a) {
   const fit::Consts C = consts_of(k);
-  const int m = *a.redo_count;
+  const int waves = list_waves(a.redo_count), step = wave_total();
   uint32_t n_bad = 0, n_fail = 0, n_redo = 0;
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < m; j += gridDim.x * blockDim.x) {
-    const int i = a.redo[j];
-    const int nh = a.tup_n[track_row(a, i)];
+  for (int w = wave_index(); w < waves; w += step) {
+    int p;
+    const int nh = list_place(a.redo_count, w, p);
+    if (p < 0) continue;
+    const int i = a.redo[redo_first(a, nh) + p];
     switch (nh) {
-      case 3:
-        if (a.cov) fit_one<3, double, HT, OT, true>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        else fit_one<3, double, HT, OT, false>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        break;
-      case 4:
-        if (a.cov) fit_one<4, double, HT, OT, true>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        else fit_one<4, double, HT, OT, false>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        break;
-      case 5:
-        if (a.cov) fit_one<5, double, HT, OT, true>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        else fit_one<5, double, HT, OT, false>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        break;
-      case 6:
-        if (a.cov) fit_one<6, double, HT, OT, true>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        else fit_one<6, double, HT, OT, false>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        break;
-      case 7:
-        if (a.cov) fit_one<7, double, HT, OT, true>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        else fit_one<7, double, HT, OT, false>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        break;
-      case 8:
-        if (a.cov) fit_one<8, double, HT, OT, true>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        else fit_one<8, double, HT, OT, false>(k, C, a, i, false, n_bad, n_fail, n_redo);
-        break;
-      default: break;
+      case 3: fit_one<3, double, HT, OT, COV>(k, C, a, i, false, n_bad, n_fail, n_redo); break;
+      case 4: fit_one<4, double, HT, OT, COV>(k, C, a, i, false, n_bad, n_fail, n_redo); break;
+      case 5: fit_one<5, double, HT, OT, COV>(k, C, a, i, false, n_bad, n_fail, n_redo); break;
+      case 6: fit_one<6, double, HT, OT, COV>(k, C, a, i, false, n_bad, n_fail, n_redo); break;
+      case 7: fit_one<7, double, HT, OT, COV>(k, C, a, i, false, n_bad, n_fail, n_redo); break;
+      default: fit_one<8, double, HT, OT, COV>(k, C, a, i, false, n_bad, n_fail, n_redo); break;
     }
     a.track_status[i] |= fit::ST_F64;
   }
@@ -422,8 +432,7 @@ __device__ inline void grad_one(const DevCfg& k, const fit::Consts& C, const Fit
   if (!ok) return;
   fit::forward<N, S>(C, f);
   if (fallback && (f.status == fit::ST_FAILED || (f.status == fit::ST_OK && double(f.cond) > C.thr))) {
-    const int slot = atomicAdd(a.redo_count, 1);
-    a.redo[slot] = i;
+    list_redo<N>(a, i);
     ++n_redo;
     return;
   }
@@ -490,86 +499,97 @@ __device__ inline void lds_clear(double* lds, int n) {
   __syncthreads();
 }
 
-// Writes (FIRST) or adds the block's module sums to its partial row.  Blocks
-// that processed no track skip the add.
+// Adds the block's module sums to its partial row (written when FIRST).
 template <bool FIRST>
-__device__ inline void lds_flush(const double* lds, int n, bool any, double* dst) {
-  const int busy = __syncthreads_or(any ? 1 : 0);
-  if (!FIRST && !busy) return;
+__device__ inline void lds_flush(const double* lds, int n, double* dst) {
+  __syncthreads();
   for (int q = threadIdx.x; q < n; q += blockDim.x) {
     if (FIRST) dst[q] = lds[q]; else dst[q] += lds[q];
   }
 }
 
-// The adjoint of the tracks with NLO..NHI hits.  Grid: kBwdBlocks persistent
-// blocks, block b owning the partial module sums partials[b].  The kernel
-// with FIRST = true runs first and initialises every partial row.
-template <int NLO, int NHI, bool FIRST, class S, class HT, class GT>
+// The portions of the adjoint are dealt out one per block first, so that few
+// of them spread over the chip, and the blocks below their number, which are
+// the ones with partial sums, own one each.
+__device__ inline int grad_first_wave() {
+  return __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x + gridDim.x * (threadIdx.x / kWave)));
+}
+
+// The adjoint.  Grid: kBwdBlocks persistent blocks, block b owning the partial
+// module sums partials[b].
+template <class S, class HT, class GT>
 __global__ void __launch_bounds__(kBlock) k_grad(DevCfg k, FitArgs a, bool fallback) {
   extern __shared__ double lds_mod[];
   const fit::Consts C = consts_of(k);
+  const int waves = list_waves(a.bin_count), step = wave_total();
+  if (static_cast<int>(blockIdx.x) >= waves) return;
   const int nm3 = a.partials ? a.n_modules * 3 : 0;
   if (nm3) lds_clear(lds_mod, nm3);
   double* lm = nm3 ? lds_mod : nullptr;
-  const int m = bin_total<NLO, NHI>(a);
   uint32_t n_redo = 0;
-  bool any = false;
   PendingGrad<GT> pend;
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < m; j += gridDim.x * blockDim.x) {
-    int nh;
-    const int i = bin_item<NLO, NHI>(a, j, nh);
-    any = true;
-    if (NLO <= 3 && 3 <= NHI && nh == 3) grad_one<3, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
-    if (NLO <= 4 && 4 <= NHI && nh == 4) grad_one<4, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
-    if (NLO <= 5 && 5 <= NHI && nh == 5) grad_one<5, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
-    if (NLO <= 6 && 6 <= NHI && nh == 6) grad_one<6, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
-    if (NLO <= 7 && 7 <= NHI && nh == 7) grad_one<7, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
-    if (NLO <= 8 && 8 <= NHI && nh == 8) grad_one<8, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
+  for (int w = grad_first_wave(); w < waves; w += step) {
+    int p;
+    const int nh = list_place(a.bin_count, w, p);
+    if (p < 0) continue;
+    const int i = a.bins[static_cast<int64_t>(nh - kMinN) * a.n_max + p];
+    switch (nh) {
+      case 3: grad_one<3, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
+      case 4: grad_one<4, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
+      case 5: grad_one<5, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
+      case 6: grad_one<6, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
+      case 7: grad_one<7, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
+      default: grad_one<8, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
+    }
   }
   if (pend.n) flush_pending(pend, a.grad_hits, k.exclusive_hits);
-  if (nm3) lds_flush<FIRST>(lds_mod, nm3, any, a.partials + static_cast<int64_t>(blockIdx.x) * nm3);
+  if (nm3) lds_flush<true>(lds_mod, nm3, a.partials + static_cast<int64_t>(blockIdx.x) * nm3);
 }
 
+// The adjoint of the listed tracks in double.
 template <class HT>
 __global__ void __launch_bounds__(kBlock) k_regrad(DevCfg k, FitArgs a) {
   extern __shared__ double lds_mod[];
   const fit::Consts C = consts_of(k);
+  const int waves = list_waves(a.redo_count), step = wave_total();
+  if (static_cast<int>(blockIdx.x) >= waves) return;  // below the number of k_grad's portions: the row is there
   const int nm3 = a.partials ? a.n_modules * 3 : 0;
   if (nm3) lds_clear(lds_mod, nm3);
-  const int m = *a.redo_count;
-  uint32_t n_redo = 0;
   double* lm = nm3 ? lds_mod : nullptr;
-  bool any = false;
+  uint32_t n_redo = 0;
   PendingGrad<float> pend;
-  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < m; j += gridDim.x * blockDim.x) {
-    const int i = a.redo[j];
-    any = true;
-    switch (a.tup_n[track_row(a, i)]) {
+  for (int w = grad_first_wave(); w < waves; w += step) {
+    int p;
+    const int nh = list_place(a.redo_count, w, p);
+    if (p < 0) continue;
+    const int i = a.redo[redo_first(a, nh) + p];
+    switch (nh) {
       case 3: grad_one<3, double, HT, float>(k, C, a, i, false, lm, n_redo, pend); break;
       case 4: grad_one<4, double, HT, float>(k, C, a, i, false, lm, n_redo, pend); break;
       case 5: grad_one<5, double, HT, float>(k, C, a, i, false, lm, n_redo, pend); break;
       case 6: grad_one<6, double, HT, float>(k, C, a, i, false, lm, n_redo, pend); break;
       case 7: grad_one<7, double, HT, float>(k, C, a, i, false, lm, n_redo, pend); break;
-      case 8: grad_one<8, double, HT, float>(k, C, a, i, false, lm, n_redo, pend); break;
-      default: break;
+      default: grad_one<8, double, HT, float>(k, C, a, i, false, lm, n_redo, pend); break;
     }
   }
   if (pend.n) flush_pending(pend, a.grad_hits, k.exclusive_hits);
-  if (nm3) lds_flush<false>(lds_mod, nm3, any, a.partials + static_cast<int64_t>(blockIdx.x) * nm3);
+  if (nm3) lds_flush<false>(lds_mod, nm3, a.partials + static_cast<int64_t>(blockIdx.x) * nm3);
 }
 
-// grad_offsets[q] += sum over blocks of partials[b][q]: each of the
+// grad_offsets[q] += sum over the blocks with tracks of partials[b][q]: each of the
 // kRedWaves wavefronts of a block sums the rows b = w, w + kRedWaves, ... of
 // 64 consecutive q in order, and the wavefronts' sums are added in order
 // (a fixed order, the same on every run).
 constexpr int kRedWaves = 16;
 
 __global__ void __launch_bounds__(kRedWaves * kWave) k_reduce_modules(const double* __restrict__ partials, int nm3,
-                                                                      int nblocks, double* __restrict__ out) {
+                                                                      const int32_t* __restrict__ bin_count,
+                                                                      double* __restrict__ out) {
   __shared__ double s_part[kRedWaves][kWave];
   const int lane = __lane_id();
   const int w = static_cast<int>(threadIdx.x) / kWave;
   const int q = blockIdx.x * kWave + lane;
+  const int nblocks = min(list_waves(bin_count), kBwdBlocks);
   double s = 0.0;
   if (q < nm3)
     for (int b = w; b < nblocks; b += kRedWaves) s += partials[static_cast<int64_t>(b) * nm3 + q];
@@ -590,9 +610,8 @@ int fit_grid(int n_max) { return grid_for(n_max, kBlock, 4096); }
 static size_t fit_scratch_bytes(int n_max, int n_modules, bool with_partials) {
   Carver c(nullptr);
   c.take<int32_t>(static_cast<size_t>(kNBins) * n_max);
-  c.take<int32_t>(kNBins);
+  c.take<int32_t>(kCounters);
   c.take<int32_t>(n_max);
-  c.take<int32_t>(1);
   if (with_partials) c.take<double>(static_cast<size_t>(kBwdBlocks) * n_modules * 3);
   return c.off + 256;
 }
@@ -618,39 +637,43 @@ static FitArgs make_args(const pt_hits& h, const DevCfg& k, const pt_ntuplets& T
   a.count = T.count;
   a.n_max = n_max;
   a.bins = c.take<int32_t>(static_cast<size_t>(kNBins) * n_max);
-  a.bin_count = c.take<int32_t>(kNBins);
+  a.bin_count = c.take<int32_t>(kCounters);
+  a.redo_count = a.bin_count + kRedoCounters;
   a.redo = c.take<int32_t>(n_max);
-  a.redo_count = c.take<int32_t>(1);
   a.partials = with_partials ? c.take<double>(static_cast<size_t>(kBwdBlocks) * k.n_modules * 3) : nullptr;
   a.status = status;
   return a;
 }
 
+template <class OT>
 static pt_err prepare(FitArgs& a, hipStream_t s) {
-  PT_HIP_CHECK(fill_i32(a.bin_count, 0, kNBins, s));
-  PT_HIP_CHECK(fill_i32(a.redo_count, 0, 1, s));
-  k_bin<<<std::min(fit_grid(a.n_max), kBinBlocks), kBlock, 0, s>>>(a);
+  PT_HIP_CHECK(fill_i32(a.bin_count, 0, kCounters, s));  // the bins' and the refit lists'
+  k_bin<OT><<<std::min(fit_grid(a.n_max), kBinBlocks), kBlock, 0, s>>>(a);
   PT_LAUNCH_CHECK();
   return PT_OK;
 }
 
 template <class S, class HT, class OT>
 static pt_err run_fit(const DevCfg& k, FitArgs& a, bool fallback, hipStream_t s) {
+  const pt_err e = prepare<OT>(a, s);
+  if (e != PT_OK) return e;
   const int g = fit_grid(a.n_max);
-  k_reject<OT><<<g, kBlock, 0, s>>>(a);
-  if (a.cov) {
-    k_fit<4, 6, S, HT, OT, true><<<g, kBlock, 0, s>>>(k, a, fallback);
-    k_fit<3, 3, S, HT, OT, true><<<g, kBlock, 0, s>>>(k, a, fallback);
-    k_fit<7, 8, S, HT, OT, true><<<g, kBlock, 0, s>>>(k, a, fallback);
+  auto launch = [&](auto kernel) { kernel<<<g, kBlock, 0, s>>>(k, a, fallback); };
+  if (a.n_max <= kMergedTracks) {
+    a.cov ? launch(k_fit<3, 8, S, HT, OT, true>) : launch(k_fit<3, 8, S, HT, OT, false>);
   } else {
-    k_fit<4, 6, S, HT, OT, false><<<g, kBlock, 0, s>>>(k, a, fallback);
-    k_fit<3, 3, S, HT, OT, false><<<g, kBlock, 0, s>>>(k, a, fallback);
-    k_fit<7, 8, S, HT, OT, false><<<g, kBlock, 0, s>>>(k, a, fallback);
+    a.cov ? launch(k_fit<4, 6, S, HT, OT, true>) : launch(k_fit<4, 6, S, HT, OT, false>);
+    a.cov ? launch(k_fit<3, 3, S, HT, OT, true>) : launch(k_fit<3, 3, S, HT, OT, false>);
+    a.cov ? launch(k_fit<7, 8, S, HT, OT, true>) : launch(k_fit<7, 8, S, HT, OT, false>);
   }
   PT_LAUNCH_CHECK();
   if (fallback) {
     // one thread per refitted track (a few percent of the tracks)
-    k_refit<HT, OT><<<grid_for(a.n_max / 16 + 1, kRefitBlock, 1024), kRefitBlock, 0, s>>>(k, a);
+    const int gr = grid_for(a.n_max / 16 + kNBins * kRefitBlock, kRefitBlock, 1024);
+    if (a.cov)
+      k_refit<HT, OT, true><<<gr, kRefitBlock, 0, s>>>(k, a);
+    else
+      k_refit<HT, OT, false><<<gr, kRefitBlock, 0, s>>>(k, a);
     PT_LAUNCH_CHECK();
   }
   return PT_OK;
@@ -666,15 +689,13 @@ pt_err launch_fit(const pt_hits& h, const DevCfg& k, const pt_ntuplets& T, const
   a.cov = out.cov;
   // one timing region over every kernel of the forward fit
   void* tok = timing_begin(s);
-  pt_err e = prepare(a, s);
-  if (e == PT_OK) {
-    const bool f64in = h.dtype == PT_F64;
-    const bool fb = precision == PT_FIT_F32_F64SOLVE;
-    if (precision == PT_FIT_F64)
-      e = f64in ? run_fit<double, double, double>(k, a, false, s) : run_fit<double, float, double>(k, a, false, s);
-    else
-      e = f64in ? run_fit<float, double, float>(k, a, fb, s) : run_fit<float, float, float>(k, a, fb, s);
-  }
+  pt_err e;
+  const bool f64in = h.dtype == PT_F64;
+  const bool fb = precision == PT_FIT_F32_F64SOLVE;
+  if (precision == PT_FIT_F64)
+    e = f64in ? run_fit<double, double, double>(k, a, false, s) : run_fit<double, float, double>(k, a, false, s);
+  else
+    e = f64in ? run_fit<float, double, float>(k, a, fb, s) : run_fit<float, float, float>(k, a, fb, s);
   timing_end(tok, "fit_fwd", s);
   return e;
 }
@@ -683,17 +704,14 @@ template <class S, class HT, class GT>
 static pt_err run_grad(const DevCfg& k, FitArgs& a, bool fallback, double* grad_offsets, hipStream_t s) {
   const size_t lds = a.partials ? static_cast<size_t>(a.n_modules) * 3 * sizeof(double) : 0;
   const int nm3 = a.n_modules * 3;
-  k_grad<4, 6, true, S, HT, GT><<<kBwdBlocks, kBlock, lds, s>>>(k, a, fallback);
-  k_grad<3, 3, false, S, HT, GT><<<kBwdBlocks, kBlock, lds, s>>>(k, a, fallback);
-  k_grad<7, 8, false, S, HT, GT><<<kBwdBlocks, kBlock, lds, s>>>(k, a, fallback);
+  k_grad<S, HT, GT><<<kBwdBlocks, kBlock, lds, s>>>(k, a, fallback);
   PT_LAUNCH_CHECK();
   if (fallback) {
     k_regrad<HT><<<kBwdBlocks, kBlock, lds, s>>>(k, a);
     PT_LAUNCH_CHECK();
   }
   if (a.partials) {
-    k_reduce_modules<<<(nm3 + kWave - 1) / kWave, kRedWaves * kWave, 0, s>>>(a.partials, nm3, kBwdBlocks,
-                                                                         grad_offsets);
+    k_reduce_modules<<<(nm3 + kWave - 1) / kWave, kRedWaves * kWave, 0, s>>>(a.partials, nm3, a.bin_count, grad_offsets);
     PT_LAUNCH_CHECK();
   }
   return PT_OK;
@@ -709,7 +727,7 @@ pt_err launch_fit_bwd(const pt_hits& h, const DevCfg& k, const pt_ntuplets& T, c
   if (!grad_offsets) a.partials = nullptr;
   // one timing region over every kernel of the adjoint
   void* tok = timing_begin(s);
-  pt_err e = prepare(a, s);
+  pt_err e = prepare<void>(a, s);
   if (e == PT_OK) {
     const bool f64in = h.dtype == PT_F64;
     const bool fb = precision == PT_FIT_F32_F64SOLVE;
