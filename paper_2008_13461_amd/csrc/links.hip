@@ -22,10 +22,10 @@
 //     in bins at least as wide as the cut angle, so that each in-cell is
 //     tested only against the out-cells of its own and the neighbouring bins
 //     (a few percent of the pairs), the examined pairs dealt out 64 at a
-//     time over the lanes.  Hits with too many out-cells for the LDS lists,
-//     and wide cuts, sweep every out-cell in a uniform loop whose loads are
-//     wave-uniform, so the R-Z test of 64 pairs costs a handful of
-//     double-precision instructions.  Pairs that pass are queued in LDS and
+//     time over the lanes.  Hits with too many out-cells for the LDS lists
+//     are binned piece by piece.  With wide cuts every out-cell is swept in a
+//     uniform loop whose loads are wave-uniform, so the R-Z test of 64 pairs
+//     costs a handful of double-precision instructions.  Pairs that pass are queued in LDS and
 //     the beam-spot test (divisions, square roots) runs on full waves of
 //     queued pairs.  Each in-cell's link count is recorded, with its links
 //     when there are at most kLocal of them, and the hit's out-cells that
@@ -50,8 +50,9 @@ constexpr int kRow = kLocal;     // record of an in-cell with links (by cell): u
 constexpr int kUnroll = 4;       // out-cells tested per step of the sweep
 constexpr int kSegment = 1 << 24;  // out-cells per queue segment (offsets fit beside the lane)
 constexpr int kSegWin = 64;        // in-cell segments of a hit handled per window (one per lane)
-constexpr int kHinBits = 2048;     // out-cells of a hit whose has_inner flag is gathered in LDS
-constexpr int kWinCap = 224;       // out-cells of the windowed search, with the copies at both ends
+constexpr int kHinBits = 1024;     // out-cells of a hit whose has_inner flag is gathered in LDS
+constexpr int kWinCap = 192;       // out-cells of the windowed search, with the copies at both ends
+constexpr int kPiece = kWinCap / 2;  // out-cells of a piece, which fits whatever its copies
 
 // Index entry of an in-cell c' = (h0, h1): its cell index, and its inner hit
 // with the BPix1 flag in the top bit.  The triplet tests rebuild the R-Z
@@ -114,8 +115,27 @@ __device__ __forceinline__ bool beam_pass(double X0, double Y0, double X1, doubl
   }
   const double U2 = ux * ux + uy * uy;
   const double V2 = vx * vx + vy * vy;
-  const double cx = (U2 * vy - V2 * uy) / Dd;
-  const double cy = (V2 * ux - U2 * vx) / Dd;
+  const double nx = U2 * vy - V2 * uy, ny = V2 * ux - U2 * vx;
+  // Two divisions and two square roots are most of this test.  With the
+  // hardware's reciprocal and reciprocal root (good to 2^-23) refined once
+  // (to 2^-45), the difference of the radii is known to 1e-13 of their sum,
+  // which decides unless it lies that close to the cut; zeros, overflows and
+  // NaN never decide (3.04 -> 2.99 ms of k_link_hits over 64 events of 200
+  // vertices).
+  {
+    double rd = __builtin_amdgcn_rcp(Dd);
+    rd = rd * __builtin_fma(-Dd, rd, 2.0);
+    const double ax = nx * rd, ay = ny * rd;
+    const double bx = X0 + ax, by = Y0 + ay;
+    const double r2 = ax * ax + ay * ay, b2 = bx * bx + by * by;
+    double p = __builtin_amdgcn_rsq(b2), q = __builtin_amdgcn_rsq(r2);
+    p = b2 * (p * __builtin_fma(-0.5 * b2 * p, p, 1.5));
+    q = r2 * (q * __builtin_fma(-0.5 * r2 * q, q, 1.5));
+    const double d = fabs(p - q), sum = p + q;
+    if (fabs(d - rmax) > 1e-12 * sum && sum > 1e-100 && sum < 1e100) return d <= rmax;
+  }
+  const double cx = nx / Dd;
+  const double cy = ny / Dd;
   const double rho2 = cx * cx + cy * cy;
   const double Cx = X0 + cx, Cy = Y0 + cy;
   const double c2 = Cx * Cx + Cy * Cy;
@@ -339,31 +359,38 @@ __global__ void k_seg_scatter(const int32_t* __restrict__ cell_count, int32_t ce
   }
 }
 
-// Per-wave LDS of k_link_hits.
-template <class T>
+// Per-wave LDS of k_link_hits; WIN: the windowed search, whose places fit 8
+// bits.  It is kept within five 1280-byte granules of the LDS, so that 24
+// wavefronts run on a CU (3.04 ms over 64 events of 200 vertices; with six
+// granules, 21 wavefronts, 3.25).
+template <class T, bool WIN>
 struct alignas(16) WaveLds {
-  int32_t queue[2 * kWave];      // queued pairs: out-cell offset << 6 | in-cell lane
-  int32_t cnt[kWave];            // links found per in-cell lane
-  uint16_t found[kWave * kLocal];  // their out-cells' offsets in the hit's out-cells (windowed search)
-  int32_t sfirst[kSegWin];       // a window of the hit's segments: first entry ...
-  int32_t spre[kSegWin + 1];     // ... and the in-cells before each (exclusive prefix)
-  int32_t segat[kWave];          // segment starting at each in-cell of a pass, or -1
-  uint32_t hin[kHinBits / 32];   // out-cells of the hit with an inner link (first kHinBits)
+  using Queue = typename std::conditional<WIN, uint16_t, int32_t>::type;
   // windowed search: the hit's out-cells by bucket (segment, offset | end-cap
   // bit << 15), bucket B - 1 copied in front and bucket 0 behind, and where
   // each bucket starts
-  double wdr[kWinCap];
-  T wz2[kWinCap];  // the outer hit's z (dz = z2 - Z1 as the doublet step computes it)
-  uint16_t wj[kWinCap];
-  uint16_t bst[kRzBuckets + 1];
+  double wdr[WIN ? kWinCap : 1];
+  T wz2[WIN ? kWinCap : 1];  // the outer hit's z (dz = z2 - Z1 as the doublet step computes it)
   // and the outer hits' x and y, by out-cell offset (values of the input
   // type, which the hit table holds exactly)
-  T wx2[kWinCap];
-  T wy2[kWinCap];
+  T wx2[WIN ? kWinCap : 1];
+  T wy2[WIN ? kWinCap : 1];
+  int32_t cnt[kWave];            // links found per in-cell lane
+  int32_t sfirst[kSegWin];       // a window of the hit's segments: first entry ...
+  int32_t segat[kWave];          // segment starting at each in-cell of a pass, or -1
+  uint32_t hin[kHinBits / 32];   // out-cells of the hit with an inner link (first kHinBits)
+  union {
+    uint8_t found[kWave * kLocal];  // the links' out-cells' offsets in the hit's out-cells (when staged whole)
+    int32_t hist[kRzBuckets];       // bucket counts, while staging
+  };
+  int32_t spre[kSegWin + 1];     // ... and the in-cells before each segment (exclusive prefix)
+  Queue queue[2 * kWave];        // queued pairs: out-cell offset << 6 | in-cell lane
+  uint16_t wj[WIN ? kWinCap : 1];
+  uint8_t bst[kRzBuckets + 1];
 };
-static_assert(kRzBuckets <= 2 * kWave, "the bucket counts use the queue, two buckets per lane");
-static_assert(kWinCap * sizeof(int32_t) <= sizeof(WaveLds<float>::found) && kWinCap <= 0x8000,
-              "staging uses the found array; offsets fit 15 bits");
+static_assert(kRzBuckets <= 2 * kWave, "the bucket counts are scanned two buckets per lane");
+static_assert(kWinCap < 256, "offsets and places of the windowed search fit 8 bits");
+static_assert(sizeof(WaveLds<float, true>) <= 5 * 1280, "24 wavefronts on a CU");
 
 template <class T>
 struct HitArgs {
@@ -393,16 +420,15 @@ struct HitArgs {
 // call it.  The windowed search (staged) keeps the links in LDS as offsets
 // in the hit's out-cells; the sweeps of larger hits write them straight to
 // the in-cell's record.
-template <class T>
-__device__ __forceinline__ void beam_batch(const DevCfg& k, const HitArgs<T>& a, WaveLds<T>& L, int nq, int cb,
-                                           int hb, double X1, double Y1, double X0l, double Y0l, int bpix1l,
-                                           int celll, bool staged) {
+template <class T, bool WIN>
+__device__ __forceinline__ void beam_batch(const DevCfg& k, const HitArgs<T>& a, WaveLds<T, WIN>& L, int nq, int cb,
+                                           int hb, double X1, double Y1, double X0l, double Y0l, int celll,
+                                           bool staged, bool whole) {
   const int lane = __lane_id();
   const int e = lane < nq ? L.queue[lane] : 0;
   const int j = e >> 6;
   const int li = e & (kWave - 1);
   const double X0 = __shfl(X0l, li, kWave), Y0 = __shfl(Y0l, li, kWave);
-  const int bpix1 = __shfl(bpix1l, li, kWave);
   const int cl = __shfl(celll, li, kWave);
   if (lane < nq) {
     double X2, Y2;
@@ -414,14 +440,15 @@ __device__ __forceinline__ void beam_batch(const DevCfg& k, const HitArgs<T>& a,
       X2 = P2.x;
       Y2 = P2.y;
     }
-    const double rmax = bpix1 ? k.rmax_bpix1 : k.rmax_other;
+    const double rmax = cl & kBpix1Bit ? k.rmax_bpix1 : k.rmax_other;
     if (beam_pass(X0, Y0, X1, Y1, X2, Y2, rmax)) {
       const int slot = atomicAdd(&L.cnt[li], 1);
       if (slot < kLocal) {
-        if (staged) {
-          L.found[li * kLocal + slot] = static_cast<uint16_t>(hb + j);
+        if (whole) {
+          L.found[li * kLocal + slot] = static_cast<uint8_t>(j);
         } else {
-          const int64_t row = slot < 4 ? cl : static_cast<int64_t>(a.cells_cap) + cl;
+          const int cell = cl & ~kBpix1Bit;
+          const int64_t row = slot < 4 ? cell : static_cast<int64_t>(a.cells_cap) + cell;
           a.spill[row * 4 + (slot & 3)] = cb + j;
         }
       }
@@ -439,13 +466,12 @@ __device__ __forceinline__ void beam_batch(const DevCfg& k, const HitArgs<T>& a,
 // is the middle hit.  Returns false (wave-uniform) when an out-cell has no
 // key or the list with its copies does not fit; the hit is then swept pair
 // by pair.
-template <class T>
-__device__ bool stage_window(const DevCfg& k, const HitArgs<T>& a, WaveLds<T>& L, int cb, int nb, double R1,
+template <class T, bool WIN>
+__device__ bool stage_window(const DevCfg& k, const HitArgs<T>& a, WaveLds<T, WIN>& L, int cb, int nb, double R1,
                              double Z1) {
   const int lane = __lane_id();
   const int B = k.rz_buckets;
-  int32_t* hist = L.queue;  // bucket counts (the queue is empty between passes)
-  int32_t* tmp = reinterpret_cast<int32_t*>(L.found);  // per out-cell: bucket | rank in the bucket << 8
+  int32_t* hist = L.hist;
   for (int b = lane; b < B; b += kWave) hist[b] = 0;
   wave_sync();
   bool bad = false;
@@ -453,22 +479,22 @@ __device__ bool stage_window(const DevCfg& k, const HitArgs<T>& a, WaveLds<T>& L
   constexpr int kRounds = (kWinCap + kWave - 1) / kWave;
   double sdr[kRounds];
   T sz2[kRounds];
-  bool send[kRounds];
+  int place[kRounds];  // bucket | rank in the bucket << 8 | end-cap << 31
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     const int j = r * kWave + lane;
     sdr[r] = 0.0;
     sz2[r] = T(0);
-    send[r] = false;
+    place[r] = 0;
     if (j < nb) {
       const double4 P2 = a.hx[a.outer[cb + j]];
       sdr[r] = P2.w - R1;  // as the doublet step computes dr and dz
       sz2[r] = static_cast<T>(P2.z);  // exact: the hit table holds values of the input type
-      send[r] = endcap_outer(k, a.pair[cb + j]);
+      const int ec = endcap_outer(k, a.pair[cb + j]) ? static_cast<int>(0x80000000u) : 0;
       const float key = rz_key(sdr[r], P2.z - Z1);
       bad |= !(key == key);
       const int b = key == key ? rz_bucket(key, B) : 0;
-      tmp[j] = b | (atomicAdd(&hist[b], 1) << 8);
+      place[r] = ec | b | (atomicAdd(&hist[b], 1) << 8);
       L.wx2[j] = static_cast<T>(P2.x);
       L.wy2[j] = static_cast<T>(P2.y);
     }
@@ -478,18 +504,13 @@ __device__ bool stage_window(const DevCfg& k, const HitArgs<T>& a, WaveLds<T>& L
   // bucket starts: exclusive scan of the counts, two buckets per lane
   const int h0 = 2 * lane < B ? hist[2 * lane] : 0;
   const int h1 = 2 * lane + 1 < B ? hist[2 * lane + 1] : 0;
-  int incl = h0 + h1;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int o = __shfl_up(incl, d, kWave);
-    if (lane >= d) incl += o;
-  }
+  const int incl = wave_incl_scan(h0 + h1);
   const int front = hist[B - 1], back = hist[0];  // copies before and after the list
   if (front + nb + back > kWinCap) return false;   // uniform
   const int ex = incl - h0 - h1;
-  if (2 * lane < B) L.bst[2 * lane] = static_cast<uint16_t>(front + ex);
-  if (2 * lane + 1 < B) L.bst[2 * lane + 1] = static_cast<uint16_t>(front + ex + h0);
-  if (lane == 0) L.bst[B] = static_cast<uint16_t>(front + nb);
+  if (2 * lane < B) L.bst[2 * lane] = static_cast<uint8_t>(front + ex);
+  if (2 * lane + 1 < B) L.bst[2 * lane + 1] = static_cast<uint8_t>(front + ex + h0);
+  if (lane == 0) L.bst[B] = static_cast<uint8_t>(front + nb);
   wave_sync();
 #pragma unroll
   for (int q = 0; q < kRounds; ++q) {
@@ -497,9 +518,8 @@ __device__ bool stage_window(const DevCfg& k, const HitArgs<T>& a, WaveLds<T>& L
     if (j >= nb) continue;
     const double dr = sdr[q];
     const T z2 = sz2[q];
-    const int v = tmp[j];
-    const int b = v & 0xFF, r = v >> 8;
-    const uint16_t jv = static_cast<uint16_t>(j | (send[q] ? 0x8000 : 0));
+    const int b = place[q] & 0xFF, r = (place[q] >> 8) & 0xFFFF;
+    const uint16_t jv = static_cast<uint16_t>(j | (place[q] < 0 ? 0x8000 : 0));
     const int at = L.bst[b] + r;
     L.wdr[at] = dr;
     L.wz2[at] = z2;
@@ -515,14 +535,22 @@ __device__ bool stage_window(const DevCfg& k, const HitArgs<T>& a, WaveLds<T>& L
   return true;
 }
 
-// One wavefront per middle hit; WAVES independent wavefronts per block.
-template <class T, int WAVES>
-__global__ void __launch_bounds__(WAVES * kWave)
+// One wavefront per middle hit; WAVES independent wavefronts per block.  A
+// hit is a chain of dependent loads and LDS round trips (5 us, 2.4 us per 64
+// in-cells and 2 us per 64 out-cells) with the vector units 64% busy, so what
+// counts are wavefronts in flight and short chains: the sweep is a kernel of
+// its own (fewer registers), the scans stay in registers, and the next
+// in-cells are loaded a pass ahead, the first ones during the staging.  64
+// events of 200 vertices, 0.9 million hits with cells on both sides: 3.94 ->
+// 2.99 ms.
+// WIN: the windowed search, for cuts narrow enough for direction bins.
+template <class T, int WAVES, bool WIN>
+__global__ void __launch_bounds__(WAVES * kWave, sizeof(T) == 4 ? 6 : 4)
     k_link_hits(DevCfg k, HitArgs<T> a) {
-  __shared__ WaveLds<T> lds[WAVES];
+  __shared__ WaveLds<T, WIN> lds[WAVES];
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int lane = __lane_id();
-  WaveLds<T>& L = lds[wave];
+  WaveLds<T, WIN>& L = lds[wave];
   const int h1 = blockIdx.x * WAVES + wave;
   if (h1 >= a.n_hits) return;
   // every load of the hit's own entries at once (all in range for h1 < n_hits)
@@ -543,89 +571,89 @@ __global__ void __launch_bounds__(WAVES * kWave)
   // the first window of the hit's in-cell segments, loaded before the staging
   int2 seg0 = make_int2(0, 0);
   if (lane < min(kSegWin, se - sb)) seg0 = a.seg[sb + lane];
+  // A window of the hit's segments (g this lane's) and the prefix of their
+  // sizes; returns its number of in-cells.
+  auto open_window = [&](int sw, int2 g) {
+    const int wn = min(kSegWin, se - sw);
+    L.sfirst[lane] = g.x;
+    const int incl = wave_incl_scan(lane < wn ? g.y : 0);
+    L.spre[lane] = incl - g.y;  // g.y = 0 past the window
+    const int aw = __builtin_amdgcn_readlane(incl, kWave - 1);
+    if (lane == 0) L.spre[kSegWin] = aw;
+    wave_sync();
+    return aw;
+  };
+  // The index entry of in-cell base + lane of the window.  Its segment: every
+  // segment overlapping the pass marks its first in-cell in it, then a prefix
+  // maximum over the lanes.
+  auto fetch = [&](int base, int aw) {
+    L.segat[lane] = -1;
+    wave_sync();
+    const int lo = L.spre[lane] - base, hi = L.spre[lane + 1] - base;
+    if (hi > 0 && lo < kWave && lo < hi) L.segat[lo > 0 ? lo : 0] = lane;
+    wave_sync();
+    const int sg = wave_max_scan(L.segat[lane]);
+    InCell e = {0, 0};
+    if (base + lane < aw) e = a.ent[L.sfirst[sg] + (base + lane - L.spre[sg])];
+    return e;
+  };
+  // the first in-cells are on their way while the out-cells are staged
+  int aw = open_window(sb, seg0);
+  InCell next = fetch(0, aw);
   // the out-cells by direction bucket, when the search can be windowed
-  const bool win = k.rz_buckets > 0 && nb <= kWinCap && stage_window(k, a, L, cb, nb, R1, Z1);
+  const bool whole = WIN && nb <= kWinCap && stage_window(k, a, L, cb, nb, R1, Z1);
+  // or else piece by piece, staged in every pass: swept, the 13 hits of an
+  // event of 200 vertices with more out-cells than fit took 80 to 99 us each
+  // (now 27) and the kernel twice the time of all others (134 -> 70 us)
+  const bool pieces = WIN && !whole;
+  bool win = whole;
+  const int seg_len = pieces ? kPiece : kSegment;
 
   for (int sw = sb; sw < se; sw += kSegWin) {
-    // a window of the hit's segments and the prefix of their sizes
-    const int wn = min(kSegWin, se - sw);
-    int c0 = 0;
-    if (lane < wn) {
-      const int2 g = sw == sb ? seg0 : a.seg[sw + lane];
-      L.sfirst[lane] = g.x;
-      c0 = g.y;
+    if (sw != sb) {
+      aw = open_window(sw, sw + lane < se ? a.seg[sw + lane] : make_int2(0, 0));
+      next = fetch(0, aw);
     }
-    int i0 = c0;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-      const int o0 = __shfl_up(i0, d, kWave);
-      if (lane >= d) i0 += o0;
-    }
-    const int aw = __builtin_amdgcn_readfirstlane(__shfl(i0, kWave - 1, kWave));  // in-cells of the window
-    L.spre[lane] = i0 - c0;
-    wave_sync();
-    if (lane == 0) L.spre[wn] = aw;
-    wave_sync();
-
     for (int base = 0; base < aw; base += kWave) {
       const int m = min(kWave, aw - base);
       // in-cell of this lane (NaN makes the R-Z test fail for idle lanes)
-      double ar = __builtin_nan(""), az = __builtin_nan(""), La = __builtin_nan("");
+      double ar = __builtin_nan(""), az = __builtin_nan("");
       double X0 = 0.0, Y0 = 0.0;  // its inner hit, for the beam-spot test
-      int bpix1 = 0;
-      int cell = -1;
-      int r = -1;  // its index entry
-      // segment of each lane's in-cell: every segment overlapping the pass
-      // marks its first in-cell in it, then a prefix maximum over the lanes
-      L.segat[lane] = -1;
-      wave_sync();
-      if (lane < wn) {
-        const int lo = L.spre[lane] - base, hi = L.spre[lane + 1] - base;
-        if (hi > 0 && lo < kWave) L.segat[lo > 0 ? lo : 0] = lane;
-      }
-      wave_sync();
-      int sg = L.segat[lane];
-#pragma unroll
-      for (int d = 1; d < kWave; d <<= 1) {
-        const int o = __shfl_up(sg, d, kWave);
-        if (lane >= d) sg = max(sg, o);
-      }
+      int cellb = 0;  // its index, with the BPix1 flag of the inner hit
       if (lane < m) {
-        const int idx = base + lane;
-        r = L.sfirst[sg] + (idx - L.spre[sg]);
-        const InCell e = a.ent[r];
-        const double4 P0 = a.hx[e.h0b & ~kBpix1Bit];
+        const double4 P0 = a.hx[next.h0b & ~kBpix1Bit];
         ar = R1 - P0.w;  // as the doublet step computes dr
         az = Z1 - P0.z;
-        La = ar * ar + az * az;
-        cell = e.cell;
+        cellb = next.cell | (next.h0b & kBpix1Bit);
         X0 = P0.x;
         Y0 = P0.y;
-        bpix1 = (e.h0b & kBpix1Bit) ? 1 : 0;
       }
+      if (base + kWave < aw) next = fetch(base + kWave, aw);
+      const double La = ar * ar + az * az;
       L.cnt[lane] = 0;
       // A partial pass with few in-cells sweeps the other way round: lanes over
       // the out-cells, the in-cells (read from their lanes) in a wave-uniform loop.
       const int out_blocks = (nb + kWave - 1) / kWave;
-      const bool transposed = m < kWave && static_cast<int64_t>(m) * out_blocks < nb;
+      const bool transposed = WIN || (m < kWave && static_cast<int64_t>(m) * out_blocks < nb);
       wave_sync();
 
       // Sweep the out-cells in segments short enough for the packed queue
       // entries (offset << 6 | lane).
-      for (int jb = 0; jb < nb; jb += kSegment) {
+      for (int jb = 0; jb < nb; jb += seg_len) {
         const int cs = cb + jb;
-        const int ns = min(kSegment, nb - jb);
+        const int ns = min(seg_len, nb - jb);
+        if (pieces) win = stage_window(k, a, L, cs, ns, R1, Z1);
         int qn = 0;  // queued pairs (uniform)
         // Queues the passing lanes of out-cell j; runs a beam batch when a full
         // wave of pairs is waiting.
         auto append = [&](int j, int li, bool pass, uint64_t mk) {
-          if (pass) L.queue[qn + lane_prefix(mk)] = (j << 6) | li;
+          if (pass) L.queue[qn + lane_prefix(mk)] = static_cast<typename WaveLds<T, WIN>::Queue>((j << 6) | li);
           qn += __popcll(mk);
           if (qn >= kWave) {
             wave_sync();
-            beam_batch(k, a, L, kWave, cs, jb, X1, Y1, X0, Y0, bpix1, cell, win);
+            beam_batch(k, a, L, kWave, cs, jb, X1, Y1, X0, Y0, cellb, win, whole);
             qn -= kWave;
-            const int t = (lane < qn) ? L.queue[kWave + lane] : 0;
+            const auto t = L.queue[kWave + lane];
             wave_sync();
             if (lane < qn) L.queue[lane] = t;
             wave_sync();
@@ -649,17 +677,13 @@ __global__ void __launch_bounds__(WAVES * kWave)
               wlen = wend - wstart;
             } else {  // no key: every out-cell once
               wstart = L.bst[0];
-              wlen = nb;
+              wlen = ns;
             }
           }
-          int incl = wlen;
-#pragma unroll
-          for (int d = 1; d < kWave; d <<= 1) {
-            const int o = __shfl_up(incl, d, kWave);
-            if (lane >= d) incl += o;
-          }
+          const int incl = wave_incl_scan(wlen);
           const int P = incl - wlen;  // first pair of this lane's range
-          const int npairs = __builtin_amdgcn_readfirstlane(__shfl(incl, kWave - 1, kWave));
+          const int npairs = __builtin_amdgcn_readlane(incl, kWave - 1);
+          const int from = wstart - P;  // pair f of the range is entry from + f
           // the pass set-up's segment marks are free now: they hold the
           // lane whose range starts at each place of a step, and a bit set
           // of those places
@@ -683,8 +707,8 @@ __global__ void __launch_bounds__(WAVES * kWave)
             const uint64_t below = sm & (lane == kWave - 1 ? ~0ull : ((2ull << lane) - 1));
             const int o = below ? starter[63 - __builtin_clzll(below)] : carry;
             carry = __builtin_amdgcn_readlane(o, kWave - 1);
-            const double oar = __shfl(ar, o, kWave), oaz = __shfl(az, o, kWave), oLa = __shfl(La, o, kWave);
-            const int at = __shfl(wstart, o, kWave) + (f - __shfl(P, o, kWave));
+            const double oar = __shfl(ar, o, kWave), oaz = __shfl(az, o, kWave), oLa = oar * oar + oaz * oaz;
+            const int at = __shfl(from, o, kWave) + f;
             bool pass = false;
             int j = 0;
             if (f < npairs) {
@@ -698,7 +722,7 @@ __global__ void __launch_bounds__(WAVES * kWave)
           }
           if (qn > 0) {
             wave_sync();
-            beam_batch(k, a, L, qn, cs, jb, X1, Y1, X0, Y0, bpix1, cell, win);
+            beam_batch(k, a, L, qn, cs, jb, X1, Y1, X0, Y0, cellb, win, whole);
           }
           wave_sync();
           continue;
@@ -724,66 +748,69 @@ __global__ void __launch_bounds__(WAVES * kWave)
           }
           if (qn > 0) {
             wave_sync();
-            beam_batch(k, a, L, qn, cs, jb, X1, Y1, X0, Y0, bpix1, cell, win);
+            beam_batch(k, a, L, qn, cs, jb, X1, Y1, X0, Y0, cellb, win, whole);
           }
           wave_sync();
           continue;
         }
-        // One out-cell at a time, wave-uniform, its segment rebuilt from the
-        // hit table; the loads of the next kUnroll out-cells are issued before
-        // the tests of the current ones.
-        auto load_out = [&](int j, double& br, double& bz, bool& ec) {
-          const double4 P2 = a.hx[a.outer[cs + j]];
-          br = P2.w - R1;
-          bz = P2.z - Z1;
-          ec = endcap_outer(k, a.pair[cs + j]);
-        };
-        double pbr[kUnroll], pbz[kUnroll];
-        bool pec[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          pbr[u] = pbz[u] = 0.0;
-          pec[u] = false;
-          if (u < ns) load_out(u, pbr[u], pbz[u], pec[u]);
-        }
-        for (int j = 0; j < ns; j += kUnroll) {
-          double cbr[kUnroll], cbz[kUnroll];
-          bool cec[kUnroll];
+        if constexpr (!WIN) {
+          // One out-cell at a time, wave-uniform, its segment rebuilt from the
+          // hit table; the loads of the next kUnroll out-cells are issued before
+          // the tests of the current ones.
+          auto load_out = [&](int j, double& br, double& bz, bool& ec) {
+            const double4 P2 = a.hx[a.outer[cs + j]];
+            br = P2.w - R1;
+            bz = P2.z - Z1;
+            ec = endcap_outer(k, a.pair[cs + j]);
+          };
+          double pbr[kUnroll], pbz[kUnroll];
+          bool pec[kUnroll];
 #pragma unroll
           for (int u = 0; u < kUnroll; ++u) {
-            cbr[u] = pbr[u];
-            cbz[u] = pbz[u];
-            cec[u] = pec[u];
+            pbr[u] = pbz[u] = 0.0;
+            pec[u] = false;
+            if (u < ns) load_out(u, pbr[u], pbz[u], pec[u]);
           }
+          for (int j = 0; j < ns; j += kUnroll) {
+            double cbr[kUnroll], cbz[kUnroll];
+            bool cec[kUnroll];
 #pragma unroll
-          for (int u = 0; u < kUnroll; ++u)
-            if (j + kUnroll + u < ns) load_out(j + kUnroll + u, pbr[u], pbz[u], pec[u]);
-          bool pass[kUnroll];
-          uint64_t mk[kUnroll];
-          uint64_t any = 0;
-#pragma unroll
-          for (int u = 0; u < kUnroll; ++u) {
-            pass[u] = j + u < ns &&
-                      rz_pass(ar, az, La, cbr[u], cbz[u], cbr[u] * cbr[u] + cbz[u] * cbz[u], cec[u] ? th2e : th2b);
-            mk[u] = __ballot(pass[u]);
-            any |= mk[u];
-          }
-          if (any) {
+            for (int u = 0; u < kUnroll; ++u) {
+              cbr[u] = pbr[u];
+              cbz[u] = pbz[u];
+              cec[u] = pec[u];
+            }
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u)
-              if (mk[u]) append(j + u, lane, pass[u], mk[u]);
+              if (j + kUnroll + u < ns) load_out(j + kUnroll + u, pbr[u], pbz[u], pec[u]);
+            bool pass[kUnroll];
+            uint64_t mk[kUnroll];
+            uint64_t any = 0;
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+              pass[u] = j + u < ns &&
+                        rz_pass(ar, az, La, cbr[u], cbz[u], cbr[u] * cbr[u] + cbz[u] * cbz[u], cec[u] ? th2e : th2b);
+              mk[u] = __ballot(pass[u]);
+              any |= mk[u];
+            }
+            if (any) {
+#pragma unroll
+              for (int u = 0; u < kUnroll; ++u)
+                if (mk[u]) append(j + u, lane, pass[u], mk[u]);
+            }
           }
-        }
-        if (qn > 0) {
+          if (qn > 0) {
+            wave_sync();
+            beam_batch(k, a, L, qn, cs, jb, X1, Y1, X0, Y0, cellb, win, whole);
+          }
           wave_sync();
-          beam_batch(k, a, L, qn, cs, jb, X1, Y1, X0, Y0, bpix1, cell, win);
         }
-        wave_sync();
       }
 
       // record the link count of each in-cell, and its links when they fit
       // the spill row; positions come from a scan afterwards
       const int n = (lane < m) ? L.cnt[lane] : 0;
+      const int cell = cellb & ~kBpix1Bit;
       if (n > 0) {
         a.out_count[cell] = n;
         if (n > kLocal) {
@@ -791,13 +818,13 @@ __global__ void __launch_bounds__(WAVES * kWave)
           a.ovf[slot] = cell;
         }
       }
-      if (win && n > 0 && n <= kLocal) {  // the links are sorted by k_link_place
+      if (whole && n > 0 && n <= kLocal) {  // the links are sorted by k_link_place
         static_assert(kRow == 8 && kLocal == 8, "a record is two 16-byte vectors");
         // two halves of 16 bytes per cell, so that the records of the cells
         // with at most four links (nearly all) are dense; places past n are
         // never read.  (The sweeps wrote their records as they went.)
         int4* sp = reinterpret_cast<int4*>(a.spill);
-        const uint16_t* fl = L.found + lane * kLocal;
+        const uint8_t* fl = L.found + lane * kLocal;
         sp[cell] = make_int4(cb + fl[0], cb + fl[1], cb + fl[2], cb + fl[3]);
         if (n > 4) sp[static_cast<int64_t>(a.cells_cap) + cell] = make_int4(cb + fl[4], cb + fl[5], cb + fl[6], cb + fl[7]);
       }
@@ -1075,7 +1102,11 @@ size_t ws_links(int n_hits, int cells_cap) {
 template <class T, int WAVES>
 static void launch_hits(const DevCfg& k, const HitArgs<T>& a, hipStream_t s) {
   const int64_t blocks = (static_cast<int64_t>(a.n_hits) + WAVES - 1) / WAVES;
-  k_link_hits<T, WAVES><<<static_cast<unsigned>(blocks < 1 ? 1 : blocks), WAVES * kWave, 0, s>>>(k, a);
+  const unsigned g = static_cast<unsigned>(blocks < 1 ? 1 : blocks);
+  if (k.rz_buckets > 0)
+    k_link_hits<T, WAVES, true><<<g, WAVES * kWave, 0, s>>>(k, a);
+  else
+    k_link_hits<T, WAVES, false><<<g, WAVES * kWave, 0, s>>>(k, a);
 }
 
 template <class T>
