@@ -412,14 +412,22 @@ __device__ inline int lane_prefix(uint64_t mask) {
 
 // Work-group dispatch places consecutive work-group ids on different XCDs
 // (round robin over kXcds), each with its own L2.  xcd_block(b, nb) renumbers
-// the nb work-groups of a 1-D grid so that each XCD takes one contiguous
-// range of the logical ids: neighbouring work-groups, which write
-// neighbouring output, then share an L2 and complete its cache lines there.
+// the nb work-groups of a 1-D grid so that each XCD takes runs of kXcdRun
+// consecutive logical ids: neighbouring work-groups, which read and write
+// neighbouring memory, then share an L2 and complete its cache lines there.
+// The runs are short, so that the layers of one event, whose hits cost very
+// different times, are spread over all XCDs (one range per XCD: the two
+// passes of the doublets over an event of 200 vertices 67 + 28 us instead of
+// 33 + 16; over 64 events 1.62 + 1.00 ms against 1.66 + 0.97).
 constexpr int kXcds = 8;
+constexpr int kXcdRun = 32;
 __device__ inline int xcd_block(int b, int nb) {
-  const int q = nb / kXcds, r = nb % kXcds;
-  const int x = b % kXcds, k = b / kXcds;
-  return x * q + min(x, r) + k;
+  constexpr int kRound = kXcds * kXcdRun;
+  const int full = nb / kRound * kRound;
+  if (b < full) return b / kRound * kRound + b % kXcds * kXcdRun + b % kRound / kXcds;
+  const int q = (nb - full) / kXcds, r = (nb - full) % kXcds;  // the last round: a range per XCD
+  const int x = (b - full) % kXcds, k = (b - full) / kXcds;
+  return full + x * q + min(x, r) + k;
 }
 
 // Orders the LDS traffic of one wavefront (its lanes run in lockstep, so a
