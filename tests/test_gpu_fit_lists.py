@@ -70,3 +70,25 @@ def test_lists_of_mixed_lengths(per_n, cap, precision_name, tol, gtol):
     num, den = (np.linalg.norm(a[rows], axis=(1, 2)) for a in (got - gh_ref, gh_ref))
     assert np.all(num <= gtol * den)
     assert np.abs(go.cpu().numpy() - go_ref).max() <= gtol * np.abs(go_ref).max()
+
+
+def test_more_wavefronts_than_a_few_rounds():
+    """Past 8192 portions of 64 tracks the order of the portions turns round: 54
+    copies of 20 000 tracks of 3 to 8 hits give the oracle's fits of one."""
+    from paper_2008_13461_amd import _abi as A
+    from paper_2008_13461_amd import api
+    n, copies = 20_000, 54     # half of them have 4 to 6 hits: 8438 portions
+    ts = E.cylinder_tracks(6, n, RADII)
+    nh = np.random.Generator(np.random.PCG64(8)).integers(3, 9, n).astype(np.uint8)
+    h = ts.hits
+    rows = torch.from_numpy(ts.tuplets).cuda().repeat(copies, 1)
+    tup = api.Tuplets.from_rows(rows, torch.from_numpy(nh).cuda().repeat(copies))
+    cfg = A.make_config(CFG)
+    tracks, status = api.Tracks.empty(n * copies, A.PT_FIT_F32_F64SOLVE), api.new_status()
+    ws = api.new_workspace(api.workspace_size(cfg, h.n_hits, 1, 0, 0, n * copies))
+    api.fit_broken_line(api.Hits.from_host(h), cfg, tup, None, A.PT_FIT_F32_F64SOLVE, tracks, status, ws)
+    ref, _, _ = O.fit(CFG, ts.tuplets, nh, h.x, h.y, h.z, h.layer)
+    got = tracks.params.view(copies, n, 5).cpu().numpy().astype(np.float64)
+    for c in (0, 1, copies - 1):
+        assert param_rel_err(got[c], ref).max() <= 1e-4
+    assert np.array_equal(got, np.broadcast_to(got[0], got.shape))
