@@ -45,6 +45,12 @@ constexpr int kCounters = kRedoCounters + kNBins;
 // with covariances take 43 us instead of 113 and 1500 take 25 instead of 40.
 constexpr int kMergedTracks = 131072;
 
+// Tracks up to which the adjoint is one kernel too: one wavefront per SIMD
+// either way, so the chains in a row count up to more tracks.  Forward and
+// adjoint of 1, 2, 4 and 8 million tracks take 0.62, 1.16, 2.14 and 4.11 ms
+// in one kernel and 0.64, 1.18, 2.12 and 4.00 in three.
+constexpr int kMergedGrads = 1 << 21;
+
 struct FitArgs {
   int32_t dtype;
   int32_t n_hits;
@@ -521,14 +527,17 @@ __device__ inline int grad_first_wave() {
   return __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x + gridDim.x * (threadIdx.x / kWave)));
 }
 
-// The adjoint.  Grid: kBwdBlocks persistent blocks, block b owning the partial
-// module sums partials[b].
-template <class S, class HT, class GT>
+// The adjoint of the tracks with NLO..NHI hits.  Grid: kBwdBlocks persistent
+// blocks, block b owning the partial module sums partials[b]; the kernel that
+// takes four hits runs first and writes the rows of all blocks with tracks of
+// any length, the others add to them.
+template <int NLO, int NHI, class S, class HT, class GT>
 __global__ void __launch_bounds__(kBlock) k_grad(DevCfg k, FitArgs a, bool fallback) {
   extern __shared__ double lds_mod[];
+  constexpr bool kFirst = NLO <= 4 && 4 <= NHI;
   const fit::Consts C = consts_of(k);
-  const int waves = list_waves(a.bin_count), step = wave_total();
-  if (static_cast<int>(blockIdx.x) >= waves) return;
+  const int waves = list_waves<NLO, NHI>(a.bin_count), step = wave_total();
+  if (static_cast<int>(blockIdx.x) >= (kFirst ? list_waves(a.bin_count) : waves)) return;
   const int nm3 = a.partials ? a.n_modules * 3 : 0;
   if (nm3) lds_clear(lds_mod, nm3);
   double* lm = nm3 ? lds_mod : nullptr;
@@ -536,20 +545,18 @@ __global__ void __launch_bounds__(kBlock) k_grad(DevCfg k, FitArgs a, bool fallb
   PendingGrad<GT> pend;
   for (int w = grad_first_wave(); w < waves; w += step) {
     int p;
-    const int nh = list_place(a.bin_count, w, p);
+    const int nh = list_place<NLO, NHI>(a.bin_count, w, p);
     if (p < 0) continue;
     const int i = a.bins[static_cast<int64_t>(nh - kMinN) * a.n_max + p];
-    switch (nh) {
-      case 3: grad_one<3, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
-      case 4: grad_one<4, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
-      case 5: grad_one<5, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
-      case 6: grad_one<6, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
-      case 7: grad_one<7, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
-      default: grad_one<8, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend); break;
-    }
+    if (NLO <= 3 && 3 <= NHI && nh == 3) grad_one<3, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
+    if (NLO <= 4 && 4 <= NHI && nh == 4) grad_one<4, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
+    if (NLO <= 5 && 5 <= NHI && nh == 5) grad_one<5, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
+    if (NLO <= 6 && 6 <= NHI && nh == 6) grad_one<6, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
+    if (NLO <= 7 && 7 <= NHI && nh == 7) grad_one<7, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
+    if (NLO <= 8 && 8 <= NHI && nh == 8) grad_one<8, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);
   }
   if (pend.n) flush_pending(pend, a.grad_hits, k.exclusive_hits);
-  if (nm3) lds_flush<true>(lds_mod, nm3, a.partials + static_cast<int64_t>(blockIdx.x) * nm3);
+  if (nm3) lds_flush<kFirst>(lds_mod, nm3, a.partials + static_cast<int64_t>(blockIdx.x) * nm3);
 }
 
 // The adjoint of the listed tracks in double.
@@ -710,7 +717,14 @@ template <class S, class HT, class GT>
 static pt_err run_grad(const DevCfg& k, FitArgs& a, bool fallback, double* grad_offsets, hipStream_t s) {
   const size_t lds = a.partials ? static_cast<size_t>(a.n_modules) * 3 * sizeof(double) : 0;
   const int nm3 = a.n_modules * 3;
-  k_grad<S, HT, GT><<<kBwdBlocks, kBlock, lds, s>>>(k, a, fallback);
+  const auto launch = [&](auto kernel) { kernel<<<kBwdBlocks, kBlock, lds, s>>>(k, a, fallback); };
+  if (a.n_max <= kMergedGrads) {
+    launch(k_grad<3, 8, S, HT, GT>);
+  } else {
+    launch(k_grad<4, 6, S, HT, GT>);
+    launch(k_grad<3, 3, S, HT, GT>);
+    launch(k_grad<7, 8, S, HT, GT>);
+  }
   PT_LAUNCH_CHECK();
   if (fallback) {
     k_regrad<HT><<<kBwdBlocks, kBlock, lds, s>>>(k, a);

@@ -16,10 +16,11 @@ pytestmark = pytest.mark.gpu
 CFG = C.default_config()
 RADII = [2.9, 4.4, 6.8, 8.6, 10.9, 13.2, 16.0, 18.2]
 MERGED = 131072      # the largest capacity of the one kernel
+GRADS = 1 << 21      # and of the adjoint's
 
 
 @pytest.mark.parametrize("per_n", [{3: 63, 4: 64, 5: 65, 6: 1, 8: 130, 2: 3, 9: 2}, {7: 1}, {2: 70}, {4: 129, 7: 64}])
-@pytest.mark.parametrize("cap", [MERGED, MERGED + 1])
+@pytest.mark.parametrize("cap", [MERGED, MERGED + 1, GRADS + 1])
 @pytest.mark.parametrize("precision_name,tol,gtol", [("PT_FIT_F64", 1e-9, 1e-8),
                                                      ("PT_FIT_F32_F64SOLVE", 1e-4, 1e-3)])
 def test_lists_of_mixed_lengths(per_n, cap, precision_name, tol, gtol):
