@@ -187,6 +187,10 @@ typedef struct {
   size_t bytes;
 } pt_workspace;
 
+/* Numbers of cells, links and rows found are counted up to 2^31 - 1, which
+ * stands for any larger one, and a capacity above 2^31 - 1 - 2^25 counts as
+ * that: more than a capacity is found exactly when the flag is set. */
+
 /* Doublets ("cells").  count[0] receives the number found, which may exceed
  * cap; only min(count, cap) entries are written (PT_FLAG_CELLS_OVERFLOW set).
  * The cells whose inner hit is h are [inner_first[h], inner_first[h] +

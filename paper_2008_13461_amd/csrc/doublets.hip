@@ -265,15 +265,15 @@ __global__ void __launch_bounds__(WAVES * kWave) k_doublets(DevCfg k, DoubletArg
   auto flush = [&]() {
     wave_sync();
     for (int i = lane; i < staged; i += kWave) {
-      const int w = pos + i;
-      if (w < a.cap) {
+      if (i < a.cap - pos) {  // pos may be kMaxCount
+        const int w = pos + i;
         a.inner[w] = hit_i;
         a.outer[w] = s_out[wave][i];
         a.pair[w] = s_pair[wave][i];
       }
     }
     wave_sync();
-    pos += staged;
+    pos = count_add(pos, staged);
     staged = 0;
   };
   // the write pass takes the groups the count pass kept instead of testing
@@ -499,8 +499,10 @@ static pt_err run_doublets(const pt_hits& h, const DevCfg& k, pt_cells& cells, u
   return PT_OK;
 }
 
-pt_err launch_doublets(const pt_hits& h, const DevCfg& k, pt_cells& cells, uint32_t* status,
+pt_err launch_doublets(const pt_hits& h, const DevCfg& k, pt_cells& out, uint32_t* status,
                        pt_workspace ws, hipStream_t s) {
+  pt_cells cells = out;
+  cells.cap = capacity(out.cap);
   if (h.dtype == PT_F64) return run_doublets<double>(h, k, cells, status, ws, s);
   return run_doublets<float>(h, k, cells, status, ws, s);
 }

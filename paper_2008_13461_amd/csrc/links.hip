@@ -878,7 +878,7 @@ __device__ __forceinline__ void emit_cell(const EmitArgs& a, int c, int cnt, int
 #pragma unroll
   for (int q = 0; q < kLocal; ++q) {
     if (q >= cnt) break;
-    if (pos + q < a.links_cap) {
+    if (q < a.links_cap - pos) {  // pos may be kMaxCount
       a.in_cell[pos + q] = c;
       a.out_cell[pos + q] = f[q];
     }
@@ -915,22 +915,24 @@ __global__ void __launch_bounds__(kTileThreads) k_link_place(EmitArgs a, uint64_
   const int off = OFF ? tile_off[tile] : 0;
   int sum = 0;
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) sum += v[i];
+  for (int i = 0; i < kScanItems; ++i) sum = count_add(sum, v[i]);
   int end;
-  int run = off + tile_exclusive(sum, !OFF && tiles > 1 ? state : nullptr, tile, s_wave, &end, [&](int i) {
+  const int in_tile = tile_exclusive(sum, !OFF && tiles > 1 ? state : nullptr, tile, s_wave, &end, [&](int i) {
     int x = 0;  // a tile before this one is full
-    for (int q = __lane_id(); q < kTileItems; q += kWave) x += a.out_count[static_cast<int64_t>(i) * kTileItems + q];
-    return wave_sum(x);
+    for (int q = __lane_id(); q < kTileItems; q += kWave)
+      x = count_add(x, a.out_count[static_cast<int64_t>(i) * kTileItems + q]);
+    return wave_count_sum(x);
   });
+  int run = count_add(off, in_tile);
   if (tile == tiles - 1 && t == 0) {
-    *total = off + end;
-    if (off + end > a.links_cap) status_flag(status, PT_FLAG_LINKS_OVERFLOW);
+    *total = count_add(off, end);
+    if (count_add(off, end) > a.links_cap) status_flag(status, PT_FLAG_LINKS_OVERFLOW);
   }
   int pos[kScanItems];
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i) {
     pos[i] = run;
-    run += v[i];
+    run = count_add(run, v[i]);
     s_pos[at + i] = pos[i];
   }
   if (t == kTileThreads - 1) s_pos[kTileItems] = run;  // the tile's end (cells past m count nothing)
@@ -995,13 +997,13 @@ __global__ void __launch_bounds__(kOvfWaves * kWave)
       wave_sync();
       for (int q = lane; q < staged; q += kWave) {
         const int c = s_link[wave][q];
-        if (w + q < links_cap) {
+        if (q < links_cap - w) {
           in_cell[w + q] = cp;
           out_cell[w + q] = c;
         }
       }
       wave_sync();
-      w += staged;
+      w = count_add(w, staged);
       staged = 0;
     };
     for (int c0 = first; c0 < last; c0 += kWave) {
@@ -1189,8 +1191,12 @@ static pt_err run_links(const pt_hits& h, const DevCfg& k, const pt_cells& cells
   return PT_OK;
 }
 
-pt_err launch_links(const pt_hits& h, const DevCfg& k, const pt_cells& cells, pt_links& L,
+pt_err launch_links(const pt_hits& h, const DevCfg& k, const pt_cells& in, pt_links& out,
                     uint32_t* status, pt_workspace ws, hipStream_t s, int block) {
+  pt_cells cells = in;
+  pt_links L = out;
+  cells.cap = capacity(in.cap);
+  L.cap = capacity(out.cap);
   if (h.dtype == PT_F64) return run_links<double>(h, k, cells, L, status, ws, s, block);
   return run_links<float>(h, k, cells, L, status, ws, s, block);
 }

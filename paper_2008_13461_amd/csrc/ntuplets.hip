@@ -209,18 +209,19 @@ __global__ void __launch_bounds__(kTileThreads) k_first_rows(TupIn a, const int3
   load_items<true>(paths, at, nr, c);  // scratch, 256-byte aligned
   int sum = 0;
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) sum += c[i];
+  for (int i = 0; i < kScanItems; ++i) sum = count_add(sum, c[i]);
   int end;
   const int first = tile_exclusive(sum, tiles > 1 ? state : nullptr, tile, s_wave, &end, [&](int i) {
     int x = 0;  // a tile before this one is full
-    for (int q = __lane_id(); q < kTileItems; q += kWave) x += paths[static_cast<int64_t>(i) * kTileItems + q];
-    return wave_sum(x);
+    for (int q = __lane_id(); q < kTileItems; q += kWave)
+      x = count_add(x, paths[static_cast<int64_t>(i) * kTileItems + q]);
+    return wave_count_sum(x);
   });
   int run = first, cnt = 0;
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i) {
-    cnt += c[i] > 0 && run < a.cap ? 1 : 0;
-    run += c[i];
+    cnt += c[i] > 0 && run < a.cap ? 1 : 0;  // at most a.cap roots in all: prod holds no more
+    run = count_add(run, c[i]);
   }
   __syncthreads();  // s_wave is read
   int n_here;
@@ -232,7 +233,7 @@ __global__ void __launch_bounds__(kTileThreads) k_first_rows(TupIn a, const int3
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i) {
     if (c[i] > 0 && run < a.cap) prod[w++] = make_int2(static_cast<int>(at + i), run);
-    run += c[i];
+    run = count_add(run, c[i]);
   }
   if (tile == tiles - 1 && threadIdx.x == 0) {
     *a.count_raw = end;
@@ -243,12 +244,15 @@ __global__ void __launch_bounds__(kTileThreads) k_first_rows(TupIn a, const int3
 // The run of cell c's outer links, [*first, *end): the links are placed in
 // cell order, so the run ends where the next cell's starts (at the total
 // after the last cell).  Both loads are issued together, so that a child's
-// run comes one dependent load after its index instead of two.
+// run comes one dependent load after its index instead of two.  Where the
+// places have saturated, the count says whether the cell has links, which lie
+// past the capacity (an end before the first: none to follow).
 __device__ inline void link_run(const TupIn& a, int c, int n_cells, int total, int* first, int* end) {
   const int f = a.out_start[c];
   const int e = a.out_start[min(c + 1, n_cells - 1)];
   *first = f;
   *end = c + 1 < n_cells ? e : total;
+  if (f == kMaxCount && a.out_count[c] > 0) *end = 0;
 }
 
 // Depth-first search from each root.  COUNT: paths[i] = rows root i emits
@@ -299,7 +303,7 @@ __global__ void k_dfs(DevCfg k, TupIn a, int32_t* __restrict__ paths, const int2
             for (int d = depth + 2; d < kMaxHits - 1; ++d) C[d] = -1;
             a.n[row] = static_cast<uint8_t>(nh);
           }
-          ++row;
+          if (row < (COUNT ? kMaxCount : a.cap)) ++row;
         }
       } else {
         ++depth;
@@ -421,9 +425,15 @@ size_t ws_ntuplets(int cells_cap, int tuplets_cap) {
   return c.off + 256;
 }
 
-pt_err launch_ntuplets(const pt_hits& h, const DevCfg& k, const pt_cells& cells, const pt_links& L,
-                       pt_ntuplets& T, uint32_t* status, pt_workspace ws, hipStream_t s) {
+pt_err launch_ntuplets(const pt_hits& h, const DevCfg& k, const pt_cells& in_cells, const pt_links& in_links,
+                       pt_ntuplets& out, uint32_t* status, pt_workspace ws, hipStream_t s) {
   (void)h;
+  pt_cells cells = in_cells;
+  pt_links L = in_links;
+  pt_ntuplets T = out;
+  cells.cap = capacity(in_cells.cap);
+  L.cap = capacity(in_links.cap);
+  T.cap = capacity(out.cap);
   Carver c(ws.ptr);
   const size_t words = state_words(cells.cap, T.cap);
   uint64_t* state = c.take<uint64_t>(words);

@@ -126,7 +126,7 @@ constexpr int64_t kLargeItems = int64_t(1) << 24;
 // dst[i] = src[0] + .. + src[i-1] over the first m = min(*n_dev, n) values,
 // n_dev a device count (n when null), dst[m] the total, which also goes to
 // *total when given, with `flag` set in the status when it exceeds cap.  src
-// and dst must not overlap.
+// and dst must not overlap.  The sums saturate (count_add below).
 struct ScanTotal {
   int32_t* total = nullptr;
   int32_t cap = 0x7fffffff;
@@ -228,6 +228,29 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
 __device__ __forceinline__ int wave_max_scan(int v) {
   return wave_scan_with(v, -0x7fffffff - 1, [](int a, int b) { return max(a, b); });
 }
+
+// Counts of cells, links and rows may exceed 32 bits (a batch with wide cuts has
+// billions of candidates): their sums saturate at kMaxCount, so that a position
+// past it lies past every capacity, which is at most kMaxItems, instead of
+// wrapping round to a place before the buffers.  Counts are not negative, so
+// the signed saturating add (one instruction) is associative on them.
+constexpr int32_t kMaxCount = 0x7fffffff;
+// What is counted as capacity: below kMaxCount, so that a saturated total always
+// exceeds it, by more than the step of any grid-stride loop over it.
+constexpr int32_t kMaxItems = kMaxCount - (1 << 25);
+inline int32_t capacity(int32_t cap) { return cap < kMaxItems ? cap : kMaxItems; }
+__device__ __forceinline__ int32_t count_add(int32_t a, int32_t b) { return __builtin_elementwise_add_sat(a, b); }
+__device__ __forceinline__ int32_t wave_count_scan(int32_t v) {
+  return wave_scan_with(v, 0, [](int a, int b) { return count_add(a, b); });
+}
+__device__ inline int32_t wave_count_sum(int32_t v) { return __builtin_amdgcn_readlane(wave_count_scan(v), kWave - 1); }
+// The exclusive prefix, from the inclusive one (a difference would not be the
+// prefix of a saturated sum).
+__device__ inline int32_t wave_before(int32_t incl) {
+  const int32_t v = __shfl_up(incl, 1, kWave);
+  return __lane_id() > 0 ? v : 0;
+}
+
 // Minimum over the wavefront, the same in every lane.
 __device__ __forceinline__ float wave_min(float v) {
   const int r = wave_scan_with(__float_as_int(v), __float_as_int(__builtin_inff()), [](int a, int b) {
@@ -291,37 +314,38 @@ __device__ inline int32_t tile_before(uint64_t* state, int tile, int32_t sum, F 
         }
       }
       const int stop = known ? __builtin_ctzll(known) : kWave;
-      before += wave_sum(lane <= stop ? static_cast<int32_t>(static_cast<uint32_t>(v[k])) : 0);
+      before = count_add(before, wave_count_sum(lane <= stop ? static_cast<int32_t>(static_cast<uint32_t>(v[k])) : 0));
       done = known != 0;
     }
   }
   if (lane == 0 && tile > 0)
-    __hip_atomic_store(state + tile, kTilePrefix | static_cast<uint32_t>(before + sum), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(state + tile, kTilePrefix | static_cast<uint32_t>(count_add(before, sum)),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return before;
 }
 
 // Exclusive prefix of v over the work-group (kTileThreads) and, with a state,
 // the tiles before its own; *end receives the sum up to and including the
 // tile, s_wave[0] the sum before it.  s_wave holds kTileThreads / kWave + 1 words.
+// The sums saturate, sum_of's as well (a sum over the wavefront: wave_count_sum).
 template <class F>
 __device__ inline int32_t tile_exclusive(int32_t v, uint64_t* state, int tile, int32_t* s_wave, int32_t* end, F sum_of) {
   constexpr int kWaves = kTileThreads / kWave;
   const int lane = __lane_id(), wave = static_cast<int>(threadIdx.x) / kWave;
-  const int32_t incl = wave_incl_scan(v);
+  const int32_t incl = wave_count_scan(v);
   if (lane == kWave - 1) s_wave[wave] = incl;
   __syncthreads();
   if (wave == 0) {
-    const int32_t w = lane < kWaves ? s_wave[lane] : 0;
-    const int32_t wi = wave_incl_scan(w);
+    const int32_t wi = wave_count_scan(lane < kWaves ? s_wave[lane] : 0);
     const int32_t sum = __builtin_amdgcn_readlane(wi, kWaves - 1);
     const int32_t before = state ? tile_before(state, tile, sum, sum_of) : 0;
-    if (lane < kWaves) s_wave[lane] = before + wi - w;
-    if (lane == 0) s_wave[kWaves] = before + sum;
+    const int32_t first = count_add(before, wave_before(wi));
+    if (lane < kWaves) s_wave[lane] = first;
+    if (lane == 0) s_wave[kWaves] = count_add(before, sum);
   }
   __syncthreads();
   *end = s_wave[kWaves];
-  return s_wave[wave] + incl - v;
+  return count_add(s_wave[wave], wave_before(incl));
 }
 __device__ inline int32_t block_exclusive(int32_t v, int32_t* s_wave, int32_t* total) {
   return tile_exclusive(v, nullptr, 0, s_wave, total, [](int) { return 0; });

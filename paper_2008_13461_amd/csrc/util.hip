@@ -28,18 +28,18 @@ __global__ void __launch_bounds__(kTileThreads) k_scan(const int32_t* __restrict
   load_items<VEC>(src, base, n, v);
   int32_t s = 0;
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) s += v[i];
+  for (int i = 0; i < kScanItems; ++i) s = count_add(s, v[i]);
   int32_t end;
   int32_t run = tile_exclusive(s, tiles > 1 ? state : nullptr, tile, s_wave, &end, [&](int i) {
     int32_t x = 0;  // a tile before this one is full
-    for (int q = __lane_id(); q < kTileItems; q += kWave) x += src[static_cast<int64_t>(i) * kTileItems + q];
-    return wave_sum(x);
+    for (int q = __lane_id(); q < kTileItems; q += kWave) x = count_add(x, src[static_cast<int64_t>(i) * kTileItems + q]);
+    return wave_count_sum(x);
   });
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i) {
     const int32_t x = v[i];
     v[i] = run;
-    run += x;
+    run = count_add(run, x);
   }
   store_items<VEC>(dst, base, n, v);
   if (tile == tiles - 1 && threadIdx.x == 0) {
@@ -61,9 +61,9 @@ __global__ void __launch_bounds__(kTileThreads) k_tile_sums(const int32_t* __res
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) v[i] = data[first + i * kTileThreads + threadIdx.x];
 #pragma unroll
-    for (int i = 0; i < kScanItems; ++i) s += v[i];
+    for (int i = 0; i < kScanItems; ++i) s = count_add(s, v[i]);
   } else {
-    for (int64_t at = first + threadIdx.x; at < n; at += kTileThreads) s += data[at];
+    for (int64_t at = first + threadIdx.x; at < n; at += kTileThreads) s = count_add(s, data[at]);
   }
   int32_t total;
   block_exclusive(s, s_wave, &total);
