@@ -271,7 +271,10 @@ __device__ __forceinline__ float wave_min(float v) {
 // counter hands out a ticket every 11 ns: 15 us for the tiles of one pileup-200
 // event.)
 constexpr uint64_t kTileSum = uint64_t(1) << 32, kTilePrefix = uint64_t(2) << 32;
-constexpr int kPolls = 256;
+#ifndef PT_TILE_POLLS
+#define PT_TILE_POLLS 256  // negative (a test build): no state is read, every work-group sums for itself
+#endif
+constexpr int kPolls = PT_TILE_POLLS;
 
 // The sum of the tiles before `tile`, whose own sum is given; called by one
 // wavefront.  sum_of(i), called by the whole wavefront, is the sum of tile i.
@@ -284,7 +287,8 @@ template <class F>
 __device__ inline int32_t tile_before(uint64_t* state, int tile, int32_t sum, F sum_of) {
   const int lane = __lane_id();
   auto load = [&](int i) {
-    return i >= 0 ? __hip_atomic_load(state + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kTilePrefix;
+    if (i < 0) return kTilePrefix;
+    return kPolls < 0 ? uint64_t(0) : __hip_atomic_load(state + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
   if (lane == 0)
     __hip_atomic_store(state + tile, (tile == 0 ? kTilePrefix : kTileSum) | static_cast<uint32_t>(sum),
