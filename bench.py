@@ -55,7 +55,7 @@ LINK_OPS_PER_CANDIDATE = 7.0
 LINK_BYTES_PER_CANDIDATE = 12.0
 LINK_BYTES_PER_LINK = 8.0
 LINK_BUCKETS_MAX = 128  # direction buckets of the windowed link search, at most
-LINK_WIN_CAP = 224      # out-cells of a hit it stages (copies included)
+LINK_PIECE = 96         # out-cells of a piece, where a hit is searched in pieces
 CELL_INDEX_BYTES_PER_CELL = 21.0
 DOUBLET_BYTES_PER_CELL = 9.0
 HBM_PEAK_GBS = 8000.0
@@ -369,10 +369,12 @@ def link_pair_counts(cells, h, cfg_d):
     """(pairs, examined): the in-cell/out-cell pairs that share a middle hit,
     and how many of them the link search tests.  The search bins a hit's
     out-cells by the direction key of their R-Z segment (B buckets) and tests
-    each in-cell against its own and the neighbouring buckets; a hit whose
-    out-cells (with the copies of the two end buckets) exceed WIN_CAP, or one
-    with a keyless out-cell, has every pair tested.  Recomputed here from the
-    hits (h.x, h.y, h.z) with the same operations, for reporting only."""
+    each in-cell against its own and the neighbouring buckets, those of a hit
+    with many out-cells piece by piece, which are the same pairs.  A hit with
+    a keyless out-cell is always searched in pieces, and every pair of a piece
+    that holds one is tested, as is every pair of a keyless in-cell.
+    Recomputed here from the hits (h.x, h.y, h.z) with the same operations,
+    for reporting only."""
     import math
 
     import numpy as np
@@ -402,17 +404,31 @@ def link_pair_counts(cells, h, cfg_d):
     key = z / (r + z.abs())
     ok = key == key
     bk = ((key + 1.0) * (0.5 * B)).nan_to_num(0.0).to(torch.int64).clamp(0, B - 1)
+    keyless = torch.zeros(n_hits, dtype=torch.int64, device=ci.device)
+    keyless.index_add_(0, ci, (~ok).long())
+    # the out-cells in pieces with a keyless one: swept, not binned
+    binned = torch.ones_like(ok)
+    swept = torch.zeros(n_hits, dtype=torch.int64, device=ci.device)
+    cut = torch.nonzero(keyless[ci] > 0).squeeze(1)
+    if cut.numel():
+        order = torch.argsort(ci[cut], stable=True)    # by middle hit, in cell order
+        cut = cut[order]
+        mid = ci[cut]
+        place = torch.arange(cut.numel(), device=ci.device) - torch.searchsorted(mid, mid)
+        new = torch.ones_like(mid, dtype=torch.bool)
+        new[1:] = (mid[1:] != mid[:-1]) | (place[1:] % LINK_PIECE == 0)
+        piece = torch.cumsum(new, 0) - 1
+        n_bad = torch.zeros(int(piece[-1].item()) + 1, dtype=torch.int64, device=ci.device)
+        n_bad.index_add_(0, piece, (~ok[cut]).long())
+        sweep = n_bad[piece] > 0
+        binned[cut[sweep]] = False
+        swept.index_add_(0, mid, sweep.long())
     hist = torch.zeros(n_hits * B, dtype=torch.int64, device=ci.device)
-    hist.index_add_(0, ci * B + bk, ok.long())
+    hist.index_add_(0, ci * B + bk, binned.long())
     hist = hist.view(n_hits, B)
-    bad = torch.zeros(n_hits, dtype=torch.int64, device=ci.device)
-    bad.index_add_(0, ci, (~ok).long())
-    win = (nb + hist[:, 0] + hist[:, B - 1] <= LINK_WIN_CAP) & (bad == 0)
-    h = co
-    w = hist[h, (bk - 1) % B] + hist[h, bk] + hist[h, (bk + 1) % B]
-    w = torch.where(ok, w, nb[h])
-    examined = torch.where(win[h], w, nb[h])
-    return pairs, int(examined.sum().item())
+    mid = co
+    w = hist[mid, (bk - 1) % B] + hist[mid, bk] + hist[mid, (bk + 1) % B] + swept[mid]
+    return pairs, int(torch.where(ok, w, nb[mid]).sum().item())
 
 
 def mixed_pileup(args, cfg_d):
