@@ -172,9 +172,43 @@ __global__ void k_vtx_mark(VtxArgs a) {
 // block takes a contiguous span of tracks, which is most often part of one
 // event, counts it in LDS (kEvSlots events from the span's first on; others
 // go to the counters directly) and adds its sums once: 0.10 and 0.04 ms.
+// Few tracks go to the counters directly, one atomic per wavefront and event: the
+// spans' barriers and second pass then cost more than the atomics, of which
+// those on one cache line, 16 or 32 events, follow one another.  The whole call,
+// directly and in spans: one event of 2048, 8192 and 16 384 tracks 50.1, 96.7,
+// 173.8 and 52.6, 97.0, 172.0 us; 64 events with 8192, 16 384 and 65 536 tracks
+// 39.1, 42.1, 58.1 and 40.8, 43.0, 52.8; 512 events with 16 384 and 65 536
+// 44.6, 49.0 and 46.7, 51.1.
 constexpr int kEvBlock = 256;
 constexpr int kEvBlocks = 2048;
 constexpr int kEvSlots = kEvBlock;
+constexpr int kFewTracks = 8192;
+constexpr int kFewPerEvent = 128;  // and these for each event
+
+__device__ inline bool few_tracks(const VtxArgs& a, int n) {
+  return n <= kFewTracks + static_cast<int64_t>(kFewPerEvent) * a.n_events;
+}
+
+// The event of a track, -1 when it takes no part.
+__device__ inline int event_of(const VtxArgs& a, int i) {
+  if (!a.use[i]) return -1;
+  const int row = a.kept ? a.kept[i] : i;
+  const int nh = a.n[row];
+  const double kap = val(a.params, static_cast<int64_t>(i) * 5 + 0, a.dbl);
+  const double z = val(a.params, static_cast<int64_t>(i) * 5 + 4, a.dbl);
+  const double v = val(a.cov, static_cast<int64_t>(i) * 15 + 14, a.dbl);
+  const double pt = a.K / fabs(kap);
+  const int h0 = a.hits[static_cast<int64_t>(row) * kMaxHits];
+  if (!(nh >= a.min_hits && pt > a.pt_min && isfinite(z) && isfinite(v) && v > 0.0 && h0 >= 0 && h0 < a.n_hits))
+    return -1;
+  // the event owning the first hit: the last e with event_offsets[e] <= h0
+  int lo = 0, hi = a.n_events - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (a.event_offsets[mid] <= h0) lo = mid; else hi = mid - 1;
+  }
+  return a.n_events > 0 && a.event_offsets[lo] <= h0 && h0 < a.event_offsets[lo + 1] ? lo : -1;
+}
 
 __device__ inline void block_span(int n, int& lo, int& hi) {
   const int64_t per = ((n + gridDim.x - 1) / gridDim.x + kEvBlock - 1) / kEvBlock * kEvBlock;
@@ -187,30 +221,20 @@ __global__ void __launch_bounds__(kEvBlock) k_vtx_events(VtxArgs a) {
   __shared__ int32_t s_first;
   int lo_i, hi_i;
   block_span(n_tracks(a), lo_i, hi_i);
+  if (few_tracks(a, n_tracks(a))) {
+    for (int i = lo_i + static_cast<int>(threadIdx.x); i < hi_i; i += kEvBlock) {
+      const int e = event_of(a, i);
+      a.ev_of[i] = e;
+      wave_add(a.ev_n, e);
+    }
+    return;
+  }
   s_cnt[threadIdx.x] = 0;
   if (threadIdx.x == 0) s_first = INT_MAX;
   __syncthreads();
   int first = INT_MAX;
   for (int i = lo_i + static_cast<int>(threadIdx.x); i < hi_i; i += kEvBlock) {
-    int e = -1;
-    if (a.use[i]) {
-      const int row = a.kept ? a.kept[i] : i;
-      const int nh = a.n[row];
-      const double kap = val(a.params, static_cast<int64_t>(i) * 5 + 0, a.dbl);
-      const double z = val(a.params, static_cast<int64_t>(i) * 5 + 4, a.dbl);
-      const double v = val(a.cov, static_cast<int64_t>(i) * 15 + 14, a.dbl);
-      const double pt = a.K / fabs(kap);
-      const int h0 = a.hits[static_cast<int64_t>(row) * kMaxHits];
-      if (nh >= a.min_hits && pt > a.pt_min && isfinite(z) && isfinite(v) && v > 0.0 && h0 >= 0 && h0 < a.n_hits) {
-        // the event owning the first hit: the last e with event_offsets[e] <= h0
-        int lo = 0, hi = a.n_events - 1;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (a.event_offsets[mid] <= h0) lo = mid; else hi = mid - 1;
-        }
-        if (a.n_events > 0 && a.event_offsets[lo] <= h0 && h0 < a.event_offsets[lo + 1]) e = lo;
-      }
-    }
+    const int e = event_of(a, i);
     a.ev_of[i] = e;
     if (e >= 0) first = min(first, e);
   }
@@ -232,6 +256,14 @@ __global__ void __launch_bounds__(kEvBlock) k_vtx_scatter(VtxArgs a) {
   __shared__ int32_t s_first;
   int lo_i, hi_i;
   block_span(n_tracks(a), lo_i, hi_i);
+  if (few_tracks(a, n_tracks(a))) {
+    for (int i = lo_i + static_cast<int>(threadIdx.x); i < hi_i; i += kEvBlock) {
+      const int e = a.ev_of[i];
+      const int slot = wave_add(a.ev_cursor, e);
+      if (e >= 0) a.list[a.ev_count[e] + slot] = i;
+    }
+    return;
+  }
   s_cnt[threadIdx.x] = 0;
   if (threadIdx.x == 0) s_first = INT_MAX;
   __syncthreads();
