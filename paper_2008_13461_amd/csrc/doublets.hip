@@ -181,6 +181,7 @@ struct DoubletArgs {
   uint8_t* pair;
   int32_t* inner_first;
   int32_t* inner_count;
+  XcdRuns xcd;             // the order of the work-groups
 };
 
 // The azimuth-bin ranges of the outer layer of pair p scanned for an inner
@@ -240,7 +241,7 @@ __global__ void __launch_bounds__(WAVES * kWave) k_doublets(DevCfg k, DoubletArg
   __shared__ int4 s_chunk[WRITE ? WAVES : 1][WRITE ? kMaskChunks : 1];
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int lane = __lane_id();
-  const int j = xcd_block(blockIdx.x, gridDim.x) * WAVES + wave;
+  const int j = xcd_block(blockIdx.x, a.xcd) * WAVES + wave;
   if (j >= a.n_hits) return;
   // count pass: the kept groups of the hit, record t on lane t
   int4 rec = make_int4(0, 0, 0, 0);
@@ -411,30 +412,43 @@ size_t ws_doublets(int n_hits, int n_events, int n_bins, int raw_cells) {
   return c.off + 256;
 }
 
-template <bool WRITE, bool ALL, class T>
-static void launch_doublets_as(const DevCfg& k, const DoubletArgs<T>& a, int n, int block, hipStream_t s) {
-  const int64_t hits = std::max(n, 1);
-  switch (block) {
-    case 64:
-      k_doublets<WRITE, 1, ALL, T><<<static_cast<unsigned>(hits), 64, 0, s>>>(k, a);
-      break;
-    case 128:
-      k_doublets<WRITE, 2, ALL, T><<<static_cast<unsigned>((hits + 1) / 2), 128, 0, s>>>(k, a);
-      break;
-    case 512:
-      k_doublets<WRITE, 8, ALL, T><<<static_cast<unsigned>((hits + 7) / 8), 512, 0, s>>>(k, a);
-      break;
-    default:
-      k_doublets<WRITE, 4, ALL, T><<<static_cast<unsigned>((hits + 3) / 4), 256, 0, s>>>(k, a);
-  }
+// The order of the work-groups over the XCDs.  Runs of 32 spread the layers of
+// an event, whose hits cost very different times, over all XCDs (one range per
+// XCD: the two passes over one event of 200 vertices 65 + 29 us instead of
+// 34 + 18, over 10 events 292 + 168 instead of 253 + 151), but every XCD's L2
+// then holds the hits of every event.  With many events the layers even out
+// within an XCD's range and the count pass, which reads an event's hits many
+// times over, is faster in ranges (64 events of 200 vertices 1545 against 1604
+// us, 256 of 50 864 against 913, 64 of 20 to 200 550 against 568); with fewer
+// that holds only where the events are alike and fill whole ranges (32 of
+// 200: 749 against 789; 48 of 20 to 200 507 against 489).  The write pass reads
+// a hit's records once: 1001 in ranges, 981 in runs.
+constexpr int kRangeEvents = 64;
+constexpr int kRoundShift = 8;  // 8 runs of 32
+
+template <bool WRITE, int WAVES, bool ALL, class T>
+static void launch_doublets_as(const DevCfg& k, DoubletArgs<T> a, int n, int n_events, hipStream_t s) {
+  const int64_t blocks = (std::max<int64_t>(n, 1) + WAVES - 1) / WAVES;
+  a.xcd = !WRITE && n_events >= kRangeEvents ? xcd_ranges(blocks) : xcd_runs(kRoundShift);
+  k_doublets<WRITE, WAVES, ALL, T><<<xcd_grid(blocks, a.xcd), WAVES * kWave, 0, s>>>(k, a);
+}
+
+template <bool WRITE, int WAVES, class T>
+static void launch_doublets_of(const DevCfg& k, const DoubletArgs<T>& a, int n, int n_events, hipStream_t s) {
+  if ((k.cut_mask & kCutsAll) == kCutsAll)
+    launch_doublets_as<WRITE, WAVES, true, T>(k, a, n, n_events, s);
+  else
+    launch_doublets_as<WRITE, WAVES, false, T>(k, a, n, n_events, s);
 }
 
 template <bool WRITE, class T>
-static void launch_doublets(const DevCfg& k, const DoubletArgs<T>& a, int n, int block, hipStream_t s) {
-  if ((k.cut_mask & kCutsAll) == kCutsAll)
-    launch_doublets_as<WRITE, true, T>(k, a, n, block, s);
-  else
-    launch_doublets_as<WRITE, false, T>(k, a, n, block, s);
+static void launch_doublets(const DevCfg& k, const DoubletArgs<T>& a, int n, int n_events, int block, hipStream_t s) {
+  switch (block) {
+    case 64: return launch_doublets_of<WRITE, 1, T>(k, a, n, n_events, s);
+    case 128: return launch_doublets_of<WRITE, 2, T>(k, a, n, n_events, s);
+    case 512: return launch_doublets_of<WRITE, 8, T>(k, a, n, n_events, s);
+    default: return launch_doublets_of<WRITE, 4, T>(k, a, n, n_events, s);
+  }
 }
 
 template <class T>
@@ -481,17 +495,17 @@ static pt_err run_doublets(const pt_hits& h, const DevCfg& k, pt_cells& cells, u
   PT_LAUNCH_CHECK();
 
   DoubletArgs<T> a{n, bin_start, valid, skey, sorted_hit, sP, sR, cnt, off, chunks, n_chunks, raw.cap, raw.inner,
-                   raw.outer, raw.pair, raw.inner_first, raw.inner_count};
+                   raw.outer, raw.pair, raw.inner_first, raw.inner_count, {}};
   const int block = (k.block_doublets == 64 || k.block_doublets == 128 || k.block_doublets == 512)
                         ? k.block_doublets : 256;
   void* tok = timing_begin(s);
-  launch_doublets<false, T>(k, a, n, block, s);
+  launch_doublets<false, T>(k, a, n, h.n_events, block, s);
   timing_end(tok, "doublets_count", s);
   PT_LAUNCH_CHECK();
   PT_HIP_CHECK(exclusive_scan(cnt, off, n, nullptr, ScanTotal{raw.count, raw.cap, PT_FLAG_CELLS_OVERFLOW, status}, cnt_state,
                               s));
   tok = timing_begin(s);
-  launch_doublets<true, T>(k, a, n, kWriteBlock, s);
+  launch_doublets<true, T>(k, a, n, h.n_events, kWriteBlock, s);
   timing_end(tok, "doublets_write", s);
   PT_LAUNCH_CHECK();
   // the Fishbone reuses the workspace behind the cells (the sorted hits are dead)

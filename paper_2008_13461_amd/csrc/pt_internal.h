@@ -439,23 +439,27 @@ __device__ inline int lane_prefix(uint64_t mask) {
 }
 
 // Work-group dispatch places consecutive work-group ids on different XCDs
-// (round robin over kXcds), each with its own L2.  xcd_block(b, nb) renumbers
-// the nb work-groups of a 1-D grid so that each XCD takes runs of kXcdRun
-// consecutive logical ids: neighbouring work-groups, which read and write
-// neighbouring memory, then share an L2 and complete its cache lines there.
-// The runs are short, so that the layers of one event, whose hits cost very
-// different times, are spread over all XCDs (one range per XCD: the two
-// passes of the doublets over an event of 200 vertices 67 + 28 us instead of
-// 33 + 16; over 64 events 1.62 + 1.00 ms against 1.66 + 0.97).
+// (round robin over kXcds), each with its own L2.  xcd_block(b, m) renumbers
+// the work-groups of a 1-D grid so that each XCD takes runs of m.run consecutive
+// logical ids: neighbouring work-groups, which read and write neighbouring
+// memory, then share an L2 and complete its cache lines there.  The grid is
+// whole rounds of kXcds runs (xcd_grid), so that there is no last round to tell
+// apart: the wavefronts issue more scalar than vector instructions before the
+// first candidate.
 constexpr int kXcds = 8;
-constexpr int kXcdRun = 32;
-__device__ inline int xcd_block(int b, int nb) {
-  constexpr int kRound = kXcds * kXcdRun;
-  const int full = nb / kRound * kRound;
-  if (b < full) return b / kRound * kRound + b % kXcds * kXcdRun + b % kRound / kXcds;
-  const int q = (nb - full) / kXcds, r = (nb - full) % kXcds;  // the last round: a range per XCD
-  const int x = (b - full) % kXcds, k = (b - full) / kXcds;
-  return full + x * q + min(x, r) + k;
+struct XcdRuns {
+  int32_t run;
+  int32_t shift;  // log2 of the ids of a round, 31 for a single round
+};
+inline XcdRuns xcd_runs(int shift) { return {(1 << shift) / kXcds, shift}; }
+inline XcdRuns xcd_ranges(int64_t nb) { return {static_cast<int32_t>((nb + kXcds - 1) / kXcds), 31}; }
+inline unsigned xcd_grid(int64_t nb, const XcdRuns& m) {
+  const int64_t round = static_cast<int64_t>(m.run) * kXcds;
+  return static_cast<unsigned>((nb + round - 1) / round * round);
+}
+__device__ inline int xcd_block(unsigned b, const XcdRuns& m) {
+  const unsigned first = b >> m.shift << m.shift;
+  return static_cast<int>(first + b % kXcds * m.run + (b - first) / kXcds);
 }
 
 // Orders the LDS traffic of one wavefront (its lanes run in lockstep, so a
