@@ -335,21 +335,26 @@ __device__ inline int wave_index() {
 }
 __device__ inline int wave_total() { return static_cast<int>(gridDim.x * blockDim.x / kWave); }
 
-// Portions beyond which the forward fit takes the shortest first: with a few
-// rounds of wavefronts or less (two or three run on a SIMD) the long fits at
-// the end are what counts (16 events with triplets, 4 to 6 hits: 81 against
-// 96 us), with many it is their start (a million tracks: 155 against 143 us).
-constexpr int kManyWaves = 8192;
+// Portions beyond which the shortest come first: with a few rounds of wavefronts
+// or less (two or three run on a SIMD) the long fits at the end are what counts
+// (16 events with triplets, 4 to 6 hits: 81 against 96 us), with many it is
+// their start (a million tracks: 155 against 143 us).  Longest and shortest
+// first, single-precision fits of 240 000, 330 000, 400 000 and 524 288
+// tracks: 85, 100, 112, 131 and 87, 94, 108, 121 us; double-precision ones of
+// 510 000, 600 000 and 800 000: 149, 162, 210 and 151, 166, 201.
+constexpr int kManyFloat = 5120;
+constexpr int kManyWaves = 8192;  // double
 
 // Forward fit of the tracks with NLO..NHI hits.
 template <int NLO, int NHI, class S, class HT, class OT, bool COV>
 __global__ void __launch_bounds__(kBlock) k_fit(DevCfg k, FitArgs a, bool fallback) {
   const fit::Consts C = consts_of(k);
   const int waves = list_waves<NLO, NHI>(a.bin_count), step = wave_total();
+  const bool shortest_first = waves > (sizeof(S) == 4 ? kManyFloat : kManyWaves);
   uint32_t n_bad = 0, n_fail = 0, n_redo = 0;
   for (int w = wave_index(); w < waves; w += step) {
     int p;
-    const int nh = list_place<NLO, NHI>(a.bin_count, waves > kManyWaves ? waves - 1 - w : w, p);
+    const int nh = list_place<NLO, NHI>(a.bin_count, shortest_first ? waves - 1 - w : w, p);
     if (p < 0) continue;
     const int i = a.bins[static_cast<int64_t>(nh - kMinN) * a.n_max + p];
     if (NLO <= 3 && 3 <= NHI && nh == 3) fit_one<3, S, HT, OT, COV>(k, C, a, i, fallback, n_bad, n_fail, n_redo);

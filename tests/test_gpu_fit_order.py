@@ -1,0 +1,42 @@
+"""The order in which the fit takes the lists of tracks of one length: shortest
+first past 5120 portions of 64 tracks in single precision."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle as O
+from synth import config as C
+from synth import events as E
+from tests.helpers import param_rel_err
+from tests.test_gpu_fit_lists import CFG, RADII
+
+pytestmark = pytest.mark.gpu
+
+
+def _copies(n, copies, seed):
+    """Host tracks of 3 to 8 hits, and their rows repeated on the GPU."""
+    from paper_2008_13461_amd import api
+    ts = E.cylinder_tracks(seed, n, RADII)
+    nh = np.random.Generator(np.random.PCG64(seed)).integers(3, 9, n).astype(np.uint8)
+    return ts, nh, api.Tuplets.from_rows(torch.from_numpy(ts.tuplets).cuda().repeat(copies, 1),
+                                         torch.from_numpy(nh).cuda().repeat(copies))
+
+
+@pytest.mark.parametrize("precision_name,tol", [("PT_FIT_F32_F64SOLVE", 1e-4), ("PT_FIT_F64", 1e-9)])
+@pytest.mark.parametrize("copies", [32, 34, 54])     # half of the tracks have 4 to 6 hits: 5000, 5313, 8438 portions
+def test_fits_in_either_order(copies, precision_name, tol):
+    from paper_2008_13461_amd import _abi as A
+    from paper_2008_13461_amd import api
+    precision = getattr(A, precision_name)
+    n = 20_000
+    ts, nh, tup = _copies(n, copies, 9)
+    h = ts.hits
+    cfg, status = A.make_config(CFG), api.new_status()
+    tracks = api.Tracks.empty(n * copies, precision)
+    ws = api.new_workspace(api.workspace_size(cfg, h.n_hits, 1, 0, 0, n * copies))
+    api.fit_broken_line(api.Hits.from_host(h), cfg, tup, None, precision, tracks, status, ws)
+    ref, _, _ = O.fit(CFG, ts.tuplets, nh, h.x, h.y, h.z, h.layer)
+    got = tracks.params.view(copies, n, 5).cpu().numpy().astype(np.float64)
+    assert param_rel_err(got[0], ref).max() <= tol
+    assert np.array_equal(got, np.broadcast_to(got[0], got.shape))
