@@ -38,17 +38,25 @@ constexpr int kRefitBlock = 64;
 // atomics would hold up every read of the bins'.
 constexpr int kRedoCounters = 64;
 constexpr int kCounters = kRedoCounters + kNBins;
-// Tracks up to which one kernel fits them whatever their number of hits (see
-// above): its registers leave one wavefront per SIMD, which costs 1.5 times the
-// time on dense lists with covariances (9.2 million triplets: 1.78 ms against 1.22)
-// and 1.07 on a million tracks without (204 us against 190), while 77 777 tracks
+// Tracks (the capacity: the number is on the device) up to which one kernel fits
+// them whatever their number of hits (see above): its registers leave one
+// wavefront per SIMD, which costs 1.5 times the time on dense lists with
+// covariances (9.2 million triplets: 1.78 ms against 1.22), while 77 777 tracks
 // with covariances take 43 us instead of 113 and 1500 take 25 instead of 40.
+// Three kernels and one, whole call in us, quadruplets and longer of 2^17, 2^18,
+// 2^19, 2^20 tracks: single precision with the refit 79, 112, 140, 207 and 63, 95,
+// 150, 244, with covariances 101, 140, 179, 265 and 82, 123, 198, 321; double
+// 71, 101, 149, 247 and 49, 79, 137, 234, with covariances 90, 132, 205, 368 and
+// 63, 107, 191, 341.  So the line lies below the crossing, which is between
+// 2^18 and 2^19 in single and near 2^21 in double precision.
 constexpr int kMergedTracks = 131072;
 
 // Tracks up to which the adjoint is one kernel too: one wavefront per SIMD
-// either way, so the chains in a row count up to more tracks.  Forward and
-// adjoint of 1, 2, 4 and 8 million tracks take 0.62, 1.16, 2.14 and 4.11 ms
-// in one kernel and 0.64, 1.18, 2.12 and 4.00 in three.
+// either way, so the chains in a row count up to more tracks.  Three kernels
+// and one, whole call in us, 2^20, 2^21 and 4 million tracks: single precision
+// with the refit and exclusive_hits 411, 765, 1331 and 393, 761, 1441, with
+// atomic additions 864, 1582, 2885 and 830, 1602, 2831; double 440, 770, 1368 and
+// 411, 758, 1412, atomic 840, 1521, 2790 and 783, 1493, 2797.
 constexpr int kMergedGrads = 1 << 21;
 
 struct FitArgs {
@@ -343,7 +351,7 @@ __device__ inline int wave_total() { return static_cast<int>(gridDim.x * blockDi
 // tracks: 85, 100, 112, 131 and 87, 94, 108, 121 us; double-precision ones of
 // 510 000, 600 000 and 800 000: 149, 162, 210 and 151, 166, 201.
 constexpr int kManyFloat = 5120;
-constexpr int kManyWaves = 8192;  // double
+constexpr int kManyWaves = 8192;  // double, and the adjoint in kernels per range
 
 // Forward fit of the tracks with NLO..NHI hits.
 template <int NLO, int NHI, class S, class HT, class OT, bool COV>
@@ -532,6 +540,39 @@ __device__ inline int grad_first_wave() {
   return __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x + gridDim.x * (threadIdx.x / kWave)));
 }
 
+// list_place with the lengths of the lists read once: in the loop over the
+// portions their loads come after the stores of the portion before, and wait
+// for them (the adjoint of 8 million tracks, single precision, exclusive_hits:
+// 2.52 against 2.40 ms).  Not in the forward fit, whose second wavefront per
+// SIMD the lengths would cost.
+template <int NLO, int NHI>
+struct Lists {
+  int count[NHI - NLO + 1];
+  __device__ explicit Lists(const int32_t* c) {
+#pragma unroll
+    for (int q = 0; q <= NHI - NLO; ++q) count[q] = __builtin_amdgcn_readfirstlane(c[NLO - kMinN + q]);
+  }
+  // Portion w: its number of hits, and this lane's place in that list (-1 past
+  // its end).  Uniform but for the place.
+  __device__ int place(int w, int& p) const {
+    int nh = 0, in = 0;
+    p = -1;
+#pragma unroll
+    for (int q = NHI - NLO; q >= 0; --q) {
+      const int waves = (count[q] + kWave - 1) / kWave;
+      if (nh == 0 && w < waves) {
+        nh = NLO + q;
+        in = count[q];
+        p = w * kWave;
+      }
+      w -= waves;
+    }
+    const int at = p + static_cast<int>(__lane_id());
+    p = nh > 0 && at < in ? at : -1;
+    return nh;
+  }
+};
+
 // The adjoint of the tracks with NLO..NHI hits.  Grid: kBwdBlocks persistent
 // blocks, block b owning the partial module sums partials[b]; the kernel that
 // takes four hits runs first and writes the rows of all blocks with tracks of
@@ -546,11 +587,17 @@ __global__ void __launch_bounds__(kBlock) k_grad(DevCfg k, FitArgs a, bool fallb
   const int nm3 = a.partials ? a.n_modules * 3 : 0;
   if (nm3) lds_clear(lds_mod, nm3);
   double* lm = nm3 ? lds_mod : nullptr;
+  const Lists<NLO, NHI> lists(a.bin_count);
+  // shortest first in a kernel per range (4 million tracks, single precision, atomic
+  // additions: 2.86 -> 2.80 ms), not in the merged one, where the long fits' own
+  // code then starts cold at the end (a million, double: 0.387 against 0.395)
+  constexpr bool kMerged = NLO == kMinN && NHI == kMaxHits;
+  const bool shortest_first = !kMerged && waves > kManyWaves;
   uint32_t n_redo = 0;
   PendingGrad<GT> pend;
   for (int w = grad_first_wave(); w < waves; w += step) {
     int p;
-    const int nh = list_place<NLO, NHI>(a.bin_count, w, p);
+    const int nh = lists.place(shortest_first ? waves - 1 - w : w, p);
     if (p < 0) continue;
     const int i = a.bins[static_cast<int64_t>(nh - kMinN) * a.n_max + p];
     if (NLO <= 3 && 3 <= NHI && nh == 3) grad_one<3, S, HT, GT>(k, C, a, i, fallback, lm, n_redo, pend);

@@ -1,5 +1,6 @@
-"""The order in which the fit takes the lists of tracks of one length: shortest
-first past 5120 portions of 64 tracks in single precision."""
+"""The order in which the fit and its adjoint take the lists of tracks of one
+length: shortest first past 5120 portions of 64 tracks in single precision, and
+past 8192 in the adjoint's kernels per range of lengths."""
 import numpy as np
 import pytest
 
@@ -9,7 +10,7 @@ import oracle as O
 from synth import config as C
 from synth import events as E
 from tests.helpers import param_rel_err
-from tests.test_gpu_fit_lists import CFG, RADII
+from tests.test_gpu_fit_lists import CFG, GRADS, RADII
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +41,29 @@ def test_fits_in_either_order(copies, precision_name, tol):
     got = tracks.params.view(copies, n, 5).cpu().numpy().astype(np.float64)
     assert param_rel_err(got[0], ref).max() <= tol
     assert np.array_equal(got, np.broadcast_to(got[0], got.shape))
+
+
+@pytest.mark.parametrize("precision_name,gtol", [("PT_FIT_F32_F64SOLVE", 1e-3), ("PT_FIT_F64", 1e-8)])
+def test_adjoint_of_many_tracks_per_range(precision_name, gtol):
+    from paper_2008_13461_amd import _abi as A
+    from paper_2008_13461_amd import api
+    precision = getattr(A, precision_name)
+    dt = torch.float64 if precision == A.PT_FIT_F64 else torch.float32
+    n, copies = 20_000, 106      # past 2^21 tracks; 16 562 portions of 4 to 6 hits, 5521 of 3, 11 041 of 7 and 8
+    assert n * copies > GRADS
+    ts, nh, tup = _copies(n, copies, 10)
+    h, off, g = ts.hits, E.module_offsets(), E.cotangents(3, n)
+    cfg, status = A.make_config(CFG), api.new_status()
+    gp, gc = (torch.from_numpy(a).cuda().to(dt).repeat((copies,) + (1,) * (a.ndim - 1)) for a in g)
+    gh = torch.zeros((h.n_hits, 3), dtype=dt, device="cuda")
+    go = torch.zeros((C.N_MODULES, 3), dtype=torch.float64, device="cuda")
+    ws = api.new_workspace(api.workspace_size(cfg, h.n_hits, 1, 0, 0, n * copies))
+    ws.fill_(0x5A)
+    api.fit_broken_line_bwd(api.Hits.from_host(h), cfg, tup, torch.from_numpy(off).cuda(), precision, gp, gc, gh, go,
+                            status, ws)
+    # every copy adds the same: the sums are `copies` times those of one
+    gh_ref, go_ref = O.fit_grad(CFG, ts.tuplets, nh, h.x, h.y, h.z, h.layer, h.module, off, g[0], g[1])
+    got = gh.cpu().numpy().astype(np.float64) / copies
+    num, den = (np.linalg.norm(a[ts.tuplets], axis=(1, 2)) for a in (got - gh_ref, gh_ref))
+    assert np.all(num <= gtol * den)
+    assert np.abs(go.cpu().numpy() / copies - go_ref).max() <= gtol * np.abs(go_ref).max()
