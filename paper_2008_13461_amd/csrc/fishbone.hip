@@ -77,15 +77,21 @@ __device__ inline int stored(const FbArgs<T>& a) {
   return c <= a.cap ? c : 0;
 }
 
+// Squared lengths, in single precision, of which a unit vector and a key are
+// formed; below the keys, the mark of a hit with a vector out of the range.
+constexpr float kMinLen2 = 1e-30f, kMaxLen2 = 1e30f, kEvery = -2.f;
+
 // Polar-direction key of a vector: uz / (|u_T| + |uz|), in [-1, 1].  As a
 // function of the angle to the z axis its slope is at most 1, and two
 // vectors at an angle a differ in that angle by at most a, so their keys
 // differ by at most a (for nearly opposite vectors, at an angle pi - a, the
-// sum of their keys is at most a in magnitude).
+// sum of their keys is at most a in magnitude).  NaN, which is never too far
+// from another key, for a vector out of the range.
 __device__ inline float polar_key(double ux, double uy, double uz) {
+  const float l2 = float((ux * ux + uy * uy) + uz * uz);
+  if (!(l2 > kMinLen2 && l2 < kMaxLen2)) return __builtin_nanf("");
   const float t = sqrtf(float(ux * ux + uy * uy));
-  const float l = t + fabsf(float(uz));
-  return l > 0.f ? float(uz) / l : 0.f;
+  return float(uz) / (t + fabsf(float(uz)));
 }
 
 // Bucket of a key in [-1, 1] among nb buckets of width 2 / nb.
@@ -300,9 +306,13 @@ __global__ void __launch_bounds__(kTierTeam[TIER]) k_fb_kill(FbArgs<T> a) {
       rmin = fminf(rmin, lr > 0.f ? ur / lr : 0.f);
       zmin = fminf(zmin, kz * zs);
       // the length is rounded once, so that it never orders two the wrong
-      // way; one whose square is out of range takes part in every test
+      // way; one whose square is out of range (a doublet of no length is
+      // aligned with every other) takes part in every test of the hit
       float l2 = float((dx * dx + dy * dy) + dz * dz);
-      if (!(l2 > 1e-30f && l2 < 1e30f)) l2 = __builtin_nanf("");
+      if (!(l2 > kMinLen2 && l2 < kMaxLen2)) {
+        l2 = __builtin_nanf("");
+        rmin = kEvery;
+      }
       const float inv = __builtin_amdgcn_rsqf(l2);
       vec[r] = make_float4(ux * inv, uy * inv, uz * inv, l2);
     }
@@ -310,7 +320,9 @@ __global__ void __launch_bounds__(kTierTeam[TIER]) k_fb_kill(FbArgs<T> a) {
     // stays above the cut angle for every cell of the hit (two nearly opposite
     // vectors cannot both point away from the beam line, or both along the
     // outer hit's side of z, by more than the cut angle)
-    const bool mirror = team_min<TEAM>(rmin, s_min) <= a.kwin && team_min<TEAM>(zmin, s_min) <= a.kwin;
+    rmin = team_min<TEAM>(rmin, s_min);
+    const bool every = rmin == kEvery;  // no buckets: each cell against all
+    const bool mirror = !every && rmin <= a.kwin && team_min<TEAM>(zmin, s_min) <= a.kwin;
     team_sync<TEAM>();
     if (t < kWave) {  // first positions: a scan over the buckets
       int carry = 0;
@@ -345,8 +357,8 @@ __global__ void __launch_bounds__(kTierTeam[TIER]) k_fb_kill(FbArgs<T> a) {
       bool killed = false;
       for (int pass = 0; pass < (mirror ? 2 : 1) && !killed; ++pass) {
         const int c = pass == 0 ? b : nb - 1 - b;
-        int q = s_bin[max(c - 1, 0)];
-        const int q1 = s_bin[min(c + 2, nb)];
+        int q = every ? 0 : s_bin[max(c - 1, 0)];
+        const int q1 = every ? m : s_bin[min(c + 2, nb)];
         while (q < q1) {
           // the next candidates within the cut angle and not longer
           uint32_t found = 0;
