@@ -192,7 +192,8 @@ typedef struct {
  * that: more than a capacity is found exactly when the flag is set. */
 
 /* Doublets ("cells").  count[0] receives the number found, which may exceed
- * cap; only min(count, cap) entries are written (PT_FLAG_CELLS_OVERFLOW set).
+ * cap; only min(count, cap) entries are written (PT_FLAG_CELLS_OVERFLOW set;
+ * with the Fishbone also those up to the number found before it).
  * The cells whose inner hit is h are [inner_first[h], inner_first[h] +
  * inner_count[h]) (clipped to cap): pt_build_doublets writes them grouped by
  * inner hit, and pt_link_cells relies on this index. */
@@ -280,8 +281,10 @@ size_t pt_workspace_size(const pt_config* cfg, int32_t n_hits, int32_t n_events,
  * uz vx - ux vz, ux vy - uy vx), W2 = (wx wx + wy wy) + wz wz and
  * U2, V2 the squared lengths in the same order, c is dropped when
  * W2 <= fishbone_theta^2 (U2 V2) and V2 < U2 (a shorter aligned doublet
- * exists).  The remaining cells keep their order, grouped by inner hit; when
- * the cells overflowed their capacity the Fishbone is not applied.
+ * exists).  The remaining cells keep their order, grouped by inner hit, and
+ * the places behind them, up to the number found before, hold the cells as
+ * they were found there; when the cells overflowed their capacity the
+ * Fishbone is not applied.
  * Requires a workspace of pt_workspace_size(cfg, hits->n_hits, hits->n_events, ...). */
 pt_err pt_build_doublets(const pt_hits* hits, const pt_config* cfg, pt_cells* cells,
                          uint32_t* status, pt_workspace ws, pt_stream stream);

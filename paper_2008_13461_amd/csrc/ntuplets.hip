@@ -359,7 +359,8 @@ __global__ void k_row_hits(TupIn a) {
 // order, one tile of kKeepTile rows per work-group, four per thread.  A
 // thread's loads go out together, level by level (with 16 rows a thread, one
 // after the other, an event's rows kept a handful of work-groups busy for 57
-// us at pileup 200).
+// us at pileup 200).  37 million rows, 36 000 tiles: 0.84 ms, where a count, a
+// scan and a write took 1.36.
 constexpr int kKeepTile = 4 * kTileThreads;
 __global__ void __launch_bounds__(kTileThreads) k_keep(TupIn a, uint64_t* state) {
   __shared__ int32_t s_wave[2 * kTileThreads / kWave + 3];

@@ -118,10 +118,13 @@ constexpr int kScanItems = 16;
 constexpr int kTileItems = kTileThreads * kScanItems;
 constexpr size_t tiles_of(int64_t n, int64_t tile) { return n > 0 ? static_cast<size_t>((n + tile - 1) / tile) : 1; }
 constexpr size_t scan_state_words(int64_t n) { return tiles_of(n, kTileItems); }
-// Above this many cells a listing takes its tiles' offsets from a pass over
-// their sums instead: the chain of states (8 ns a tile) is then longer than
-// the pass (64 PU200 events, 47 000 tiles: k_link_place 1.28 ms in one kernel,
-// 0.75 after 0.16; one PU200 event, 730 tiles: 25 us in one, 30 with the pass).
+// Above this many cells (the capacity) a listing takes its tiles' offsets from a
+// pass over their sums instead: the chain of states (8 ns a tile) is then longer
+// than the pass.  In one kernel and with the pass, 1, 2, 4, 8 and 64 events of
+// 200 vertices (740, 1470, 2940, 5860 and 46 700 tiles): pt_link_cells 133, 214,
+// 416, 796, 5713 and 134, 211, 406, 759, 5314 us, pt_find_ntuplets 84, 107, 168,
+// 272, 1704 and 89, 105, 157, 243, 1352 us.  The line, 4096 tiles of capacity,
+// lies above the crossing, which is near 1000 tiles of cells.
 constexpr int64_t kLargeItems = int64_t(1) << 24;
 // dst[i] = src[0] + .. + src[i-1] over the first m = min(*n_dev, n) values,
 // n_dev a device count (n when null), dst[m] the total, which also goes to
