@@ -875,9 +875,10 @@ def profile_fishbone_run(args):
 
 
 def profile_workflows_run(args):
-    """Two eager passes of each workflow on the PU200 batch (reconstruction,
-    fit with covariance, ambiguity resolution, vertices), with the bench's
-    fixed settings, for kernel traces of the stages after the fit."""
+    """Two eager runs of the quadruplet workflow, then two of the triplet one,
+    on the PU200 batch (reconstruction, fit with covariance, ambiguity
+    resolution, vertices), with the bench's fixed settings, for kernel traces
+    of the stages after the fit."""
     import torch
 
     from paper_2008_13461_amd import _abi as A

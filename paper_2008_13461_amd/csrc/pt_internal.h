@@ -263,7 +263,8 @@ __device__ __forceinline__ float wave_min(float v) {
 }
 
 // ---------------------------------------------------------------------------
-// Prefixes over the tiles of one kernel, tile i the work-group i.  The state of
+// Prefixes over the tiles of one kernel (decoupled look-back), tile i the
+// work-group i.  The state of
 // a tile is a value in the low word, and above it 0 (not there yet), kTileSum
 // (the tile's own sum) or kTilePrefix (the sum up to and including it).  Value
 // and flag are one atomic, so no other memory is ordered by it.  A work-group
